@@ -387,27 +387,36 @@ at_status at_ensemble_create(int n_trees, int depth, int n_features, const uint8
     if (depth < 1 || depth > 12) return fail(AT_E_UNSUPPORTED, "at_ensemble_create: depth out of [1, 12]");
     if (n_features < 1 || n_features > 256) return fail(AT_E_UNSUPPORTED, "at_ensemble_create: n_features out of [1, 256]");
     const size_t n_int = ((size_t)1 << depth) - 1, n_leaf = (size_t)1 << depth, W = (size_t)2 << depth;
+    // which results the compact forms' six-bit thresholds give exactly
+    bool score6 = true, leaf6 = true;
+    for (size_t t = 0; t < (size_t)n_trees; ++t)
+        for (size_t n = 0, first = 0, span = n_leaf; n < n_int; ++n) {
+            // node n covers the leaves [(n - first) * span, + span) of its
+            // tree; `first` is the first node of its level
+            if (n == 2 * first + 1) {
+                first = n;
+                span /= 2;
+            }
+            if (fid[t * n_int + n] >= n_features)
+                return fail(AT_E_INVALID, "at_ensemble_create: split feature >= n_features");
+            if (thr[t * n_int + n] <= NODE_THR_MAX) continue;
+            leaf6 = false;
+            const float* v = leaf + t * n_leaf + (n - first) * span;
+            for (size_t j = 1; j < span && score6; ++j) score6 = std::memcmp(&v[0], &v[j], 4) == 0;
+        }
     std::vector<uint32_t> words;
     // padded to whole 32 KB blocks so that chunked prefetches stay in bounds
-    const size_t padded = ((size_t)n_trees * W + ENSEMBLE_PAD_WORDS - 1) / ENSEMBLE_PAD_WORDS * ENSEMBLE_PAD_WORDS;
     try {
-        words.assign(padded, 0u);
+        words.assign(((size_t)n_trees * W + ENSEMBLE_PAD_WORDS - 1) / ENSEMBLE_PAD_WORDS * ENSEMBLE_PAD_WORDS, 0u);
     } catch (...) {
         return fail(AT_E_OOM, "at_ensemble_create: host allocation");
     }
     for (size_t t = 0; t < (size_t)n_trees; ++t) {
         uint32_t* tw = words.data() + t * W;
-        for (size_t n = 0; n < n_int; ++n) {
-            const uint8_t f = fid[t * n_int + n];
-            if (f >= n_features) return fail(AT_E_INVALID, "at_ensemble_create: split feature >= n_features");
-            // heap node n (0-based) is word n + 1
-            tw[n + 1] = ((uint32_t)thr[t * n_int + n] << 16) | tile_offset(f);
-        }
-        for (size_t j = 0; j < n_leaf; ++j) {
-            uint32_t bits;
-            std::memcpy(&bits, &leaf[t * n_leaf + j], 4);
-            tw[n_leaf + j] = bits;
-        }
+        // heap node n (0-based) is word n + 1
+        for (size_t n = 0; n < n_int; ++n)
+            tw[n + 1] = ((uint32_t)thr[t * n_int + n] << 16) | tile_offset(fid[t * n_int + n]);
+        std::memcpy(tw + n_leaf, &leaf[t * n_leaf], n_leaf * 4);
     }
     // compact form for the annealing kernels (layout in at_internal.h)
     const size_t NB = n_leaf / 2, W16 = NB + n_leaf;
@@ -499,6 +508,8 @@ at_status at_ensemble_create(int n_trees, int depth, int n_features, const uint8
     e->desc.depth = depth;
     e->desc.n_features = n_features;
     e->desc.words_per_tree = (int32_t)W;
+    e->desc.score6 = score6 ? 1 : 0;
+    e->desc.leaf6 = leaf6 ? 1 : 0;
     e->desc.words = static_cast<const uint32_t*>(e->d_words.p);
     e->desc.words16 = static_cast<const uint32_t*>(e->d_words16.p);
     e->desc.words32 = static_cast<const uint32_t*>(e->d_words32.p);

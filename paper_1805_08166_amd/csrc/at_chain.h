@@ -190,5 +190,112 @@ __device__ __forceinline__ void group_offer(at_entry* list, Rec& rec, int k, int
     "v_and_or_b32 %11, %3, %24, %25\n\t"                                                                   \
     "v_lshl_add_u32 %15, %7, 2, %29"
 
+constexpr uint32_t LOCAL_TILE_MASK = 0x3f03u;  // node bits of a byte address in a 64-column tile (below 16 KB)
+
+// Leaf indices of four trees for this lane: nb holds the LDS byte addresses
+// of the trees' node blocks (per lane), fb the lane's tile column.  The
+// levels are those of the tree kernel's walk (five vector instructions per
+// level and tree); trees are independent, so their LDS round trips overlap.
+// The reads are issued with absolute LDS addresses from inline asm (the
+// compiler would add the dynamic LDS base to every address) and waited for
+// in the same statement.
+template <int DEPTH>
+__device__ __forceinline__ void walk4_local(const uint32_t (&nb)[4], uint32_t fb, uint32_t (&q)[4]) {
+    uint32_t node[4], p[4], fa[4], pa[4];
+    asm volatile(
+        "ds_read_u16 %0, %4\n\t"
+        "ds_read_u16 %1, %5\n\t"
+        "ds_read_u16 %2, %6\n\t"
+        "ds_read_u16 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(node[0]), "=&v"(node[1]), "=&v"(node[2]), "=&v"(node[3])
+        : "v"(nb[0]), "v"(nb[1]), "v"(nb[2]), "v"(nb[3]));
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        p[g] = 1u;
+        fa[g] = (node[g] & LOCAL_TILE_MASK) | fb;
+        pa[g] = nb[g] + 4u;
+    }
+#pragma unroll
+    for (int l = 0; l + 1 < DEPTH; ++l) {
+        uint32_t x4[4], pr[4];
+        asm volatile(
+            "ds_read_u8 %0, %8\n\t"
+            "ds_read_b32 %4, %12\n\t"
+            "ds_read_u8 %1, %9\n\t"
+            "ds_read_b32 %5, %13\n\t"
+            "ds_read_u8 %2, %10\n\t"
+            "ds_read_b32 %6, %14\n\t"
+            "ds_read_u8 %3, %11\n\t"
+            "ds_read_b32 %7, %15\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(x4[0]), "=&v"(x4[1]), "=&v"(x4[2]), "=&v"(x4[3]), "=&v"(pr[0]), "=&v"(pr[1]), "=&v"(pr[2]),
+              "=&v"(pr[3])
+            : "v"(fa[0]), "v"(fa[1]), "v"(fa[2]), "v"(fa[3]), "v"(pa[0]), "v"(pa[1]), "v"(pa[2]), "v"(pa[3]));
+        const uint32_t mask = LOCAL_TILE_MASK;
+        asm(AT_WALK4_ASM
+            : "+v"(node[0]), "+v"(node[1]), "+v"(node[2]), "+v"(node[3]), "+v"(p[0]), "+v"(p[1]), "+v"(p[2]),
+              "+v"(p[3]), "=&v"(fa[0]), "=&v"(fa[1]), "=&v"(fa[2]), "=&v"(fa[3]), "=&v"(pa[0]), "=&v"(pa[1]),
+              "=&v"(pa[2]), "=&v"(pa[3])
+            : "v"(x4[0]), "v"(x4[1]), "v"(x4[2]), "v"(x4[3]), "v"(pr[0]), "v"(pr[1]), "v"(pr[2]), "v"(pr[3]),
+              "s"(mask), "v"(fb), "v"(nb[0]), "v"(nb[1]), "v"(nb[2]), "v"(nb[3])
+            : "vcc");
+    }
+    uint32_t x4[4];
+    asm volatile(
+        "ds_read_u8 %0, %4\n\t"
+        "ds_read_u8 %1, %5\n\t"
+        "ds_read_u8 %2, %6\n\t"
+        "ds_read_u8 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(x4[0]), "=&v"(x4[1]), "=&v"(x4[2]), "=&v"(x4[3])
+        : "v"(fa[0]), "v"(fa[1]), "v"(fa[2]), "v"(fa[3]));
+#pragma unroll
+    for (int g = 0; g < 4; ++g) q[g] = 2u * p[g] + (x4[g] >= (node[g] & 0xffu) ? 1u : 0u) - (1u << DEPTH);
+}
+
+// Adds the leaf values row[0 .. nt) to s in order (row 16-byte aligned):
+// blocks of sixteen float4 reads in flight, then their 64 adds; the rest in
+// batches of 8, 4, 2 and 1 float4.  Nothing is carried from one block to
+// the next but s, so the compiler has no registers to shuffle between
+// blocks, and every branch is uniform (no selects in the chain of adds).
+__device__ __forceinline__ void add4(float& s, const float4& v) {
+    s = s + v.x;
+    s = s + v.y;
+    s = s + v.z;
+    s = s + v.w;
+}
+
+template <int B>
+__device__ __forceinline__ void fold_block(float& s, const float4* __restrict__ r4) {
+    float4 R[B];
+#pragma unroll
+    for (int g = 0; g < B; ++g) R[g] = r4[g];
+#pragma unroll
+    for (int g = 0; g < B; ++g) add4(s, R[g]);
+}
+
+__device__ __forceinline__ float fold_row(float s, const float* __restrict__ row, int nt) {
+    const float4* r4 = reinterpret_cast<const float4*>(row);
+    const int n4 = nt >> 2;
+    int i = 0;
+    for (; i + 16 <= n4; i += 16) fold_block<16>(s, r4 + i);
+    if (n4 - i >= 8) {
+        fold_block<8>(s, r4 + i);
+        i += 8;
+    }
+    if (n4 - i >= 4) {
+        fold_block<4>(s, r4 + i);
+        i += 4;
+    }
+    if (n4 - i >= 2) {
+        fold_block<2>(s, r4 + i);
+        i += 2;
+    }
+    if (n4 - i >= 1) fold_block<1>(s, r4 + i);
+    for (int t = n4 * 4; t < nt; ++t) s = s + row[t];
+    return s;
+}
+
 }  // namespace dev
 }  // namespace at

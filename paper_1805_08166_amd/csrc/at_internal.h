@@ -67,18 +67,28 @@ constexpr int STAGE_CHAINS = 16;         // chains per chain-kernel workgroup
 // and 2m+1) holding (thr << 16) | tile byte offset of its feature; words
 // 2^d .. 2^(d+1)-1 hold the leaf values (float bits); word 0 is unused.
 //
-// The annealing path uses a second, compact form (words16): its features
-// are loop-context bitlens, never above 31, so a split on x < thr decides
-// the same with thr clamped to 32.  Tree t occupies words16 [t*W16,
-// (t+1)*W16) with W16 = 3 * 2^(d-1): a node block of 2^(d-1) words (word 0
-// holds the root in its low half, word p >= 1 holds internal nodes 2p and
-// 2p+1 as the low and high halves) followed by the 2^d leaf values.  A
-// 16-bit node is (f & 3) | min(thr, 32) << 2 | (f >> 2) << 8.
+// The other paths use a second, compact form (words16) whose thresholds
+// have six bits.  Tree t occupies words16 [t*W16, (t+1)*W16) with W16 = 3 *
+// 2^(d-1): a node block of 2^(d-1) words (word 0 holds the root in its low
+// half, word p >= 1 holds internal nodes 2p and 2p+1 as the low and high
+// halves) followed by the 2^d leaf values.  A 16-bit node is (f & 3) |
+// min(thr, 63) << 2 | (f >> 2) << 8.
+//   - Annealing features are loop-context bitlens, never above 31, so a
+//     split on x < thr decides the same with thr clamped to 63.
+//   - Batched scoring takes any feature values: with x clamped to 63 the
+//     clamped split decides the same wherever thr <= 63.  score6 says that
+//     every node has thr <= 63 or reaches one leaf value whichever way it
+//     goes (the splits that pad a trained tree), so the scores are those of
+//     the tables; leaf6 that every node has thr <= 63, so the leaf indices
+//     are as well.
+// The forms below with compact nodes follow the same rule.
 struct EnsembleDesc {
     int32_t n_trees;
     int32_t depth;
     int32_t n_features;
     int32_t words_per_tree;
+    int32_t score6;
+    int32_t leaf6;
     const uint32_t* words;
     const uint32_t* words16;
     // Local forms for the chain-local annealing path: the compact form's
@@ -107,12 +117,12 @@ struct EnsembleDesc {
     const uint32_t* words32;
 };
 
-// Largest threshold the compact form keeps; annealing features never exceed
-// SA_FEATURE_MAX.
+// Annealing features never exceed SA_FEATURE_MAX; the compact form keeps
+// thresholds up to NODE_THR_MAX, above it.
 constexpr uint32_t SA_FEATURE_MAX = 31;
-constexpr uint32_t SA_THR_CLAMP = SA_FEATURE_MAX + 1;
+constexpr uint32_t NODE_THR_MAX = 63;
 __host__ __device__ inline uint32_t node16(uint32_t f, uint32_t thr) {
-    const uint32_t t = thr < SA_THR_CLAMP ? thr : SA_THR_CLAMP;
+    const uint32_t t = thr < NODE_THR_MAX ? thr : NODE_THR_MAX;
     return (f & 3u) | (t << 2) | ((f >> 2) << 8);
 }
 
@@ -278,8 +288,13 @@ hipError_t launch_feature_scan(const at_space_s& sp, uint32_t* flags, uint32_t* 
 // accumulate: add to scores (fp32, the stored value first) instead of storing
 hipError_t launch_predict(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores,
                           uint16_t* leaves, bool accumulate, hipStream_t stream);
+// Scoring by the compact forms (at_score.hip): needs score6, and leaf6 with
+// leaves.
 hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores,
                         uint16_t* leaves, bool accumulate, hipStream_t stream);
+// Scoring by `words` (any thresholds), rows of 28, 44 or 48 feature quads.
+hipError_t launch_score_wide(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores,
+                             uint16_t* leaves, bool accumulate, hipStream_t stream);
 // eg: the global model of an Eq. 4 run (over the relation features), or null.
 hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const EnsembleDesc* eg, at_chains_s& ch,
                         int steps, bool init, const float* thr, at_entry* best, at_entry* trace, hipStream_t stream);

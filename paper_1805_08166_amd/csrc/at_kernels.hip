@@ -468,10 +468,11 @@ hipError_t predict_depth(const EnsembleDesc& e, const int32_t* feats, int64_t n,
 hipError_t launch_predict(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores,
                           uint16_t* leaves, bool accumulate, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    // conv2d loop-feature rows (176) and relation-feature rows (192), 16-byte
-    // aligned, take the tuned kernel
-    if ((e.n_features == 176 || e.n_features == 192) && (reinterpret_cast<uintptr_t>(feats) & 15u) == 0)
-        return launch_score(e, feats, n, scores, leaves, accumulate, stream);
+    // thresholds within six bits: the compact forms, any size and alignment
+    if (leaves ? e.leaf6 : e.score6) return launch_score(e, feats, n, scores, leaves, accumulate, stream);
+    const int quads = (e.n_features + 3) / 4;
+    if (quads == 28 || quads == 44 || quads == 48)
+        return launch_score_wide(e, feats, n, scores, leaves, accumulate, stream);
     switch (e.depth) {
         case 1: return predict_depth<1>(e, feats, n, scores, leaves, accumulate, stream);
         case 2: return predict_depth<2>(e, feats, n, scores, leaves, accumulate, stream);

@@ -1,14 +1,14 @@
-// Batched ensemble scoring for conv2d feature rows: 176 loop-context
-// features or 192 context relation features (44 or 48 feature quads).
-//
-// One candidate per lane, 256 per workgroup.  LDS holds one chunk of packed
-// tree words (8 KB, 32 KB for depth 12) followed by the workgroup's feature
-// tile (176 u8 per row, quad-major), 53 KB in all at depth 8 so that three
-// workgroups share a compute unit.  The next chunk is fetched into registers
-// while the current one is walked; the walk keeps GROUP trees in flight per
-// lane and needs one LDS round trip per level (walk_pair).  Scores are the
-// fp32 sum of the reached leaves in tree order, starting from +0.0f.
-#include "at_device.h"
+// Batched ensemble scoring.  Two kernels, both giving the fp32 sum of the
+// reached leaves in tree order from +0.0f (and the leaf indices):
+//   k_rows   up to 64 rows a workgroup, a row's trees spread over its lanes
+//            and waves (compact forms): any size, row length and alignment
+//   k_score  256 rows a workgroup, a lane walks every tree of its row
+//            (32-bit node words): large batches, and ensembles with
+//            thresholds above six bits, of 28, 44 or 48 feature quads (GEMM
+//            and conv2d loop-context rows, relation rows)
+#include <algorithm>
+
+#include "at_chain.h"
 
 namespace at {
 namespace {
@@ -16,6 +16,171 @@ namespace {
 using namespace dev;
 
 constexpr int SWG = 256;
+
+// ==========================================================================
+// k_rows.  A workgroup scores R rows (a power of two up to 64).  Their
+// features sit in a 64-column byte tile at LDS address 0 (byte (f & 3) of
+// dword (f >> 2) * 64 + column holds 4x+3, x clamped to [0, 63]; column l
+// holds row l % R), so every lane reads its own bank.  The trees pass through
+// two LDS buffers in chunks; while chunk k is walked, its successor is on
+// its way (direct-to-LDS loads of every wave) and wave 0 folds the leaf
+// values of chunk k - 1, one lane per row.  One barrier a chunk.
+//
+// A walk lane takes row lane % R and four consecutive trees of the chunk.
+// TAIL: only levels 0 .. d-2 are streamed (local_top) and the last level
+// with its leaf comes from the tree's 16-byte tail record; else whole trees
+// (local_full).
+//
+// One lane a row (k_score, the only way before) leaves the chip idle below
+// some 200 K rows: every row's trees are one lane's chain of dependent LDS
+// reads.  Here the chain is a chunk's walk, then the fold's dependent adds.
+// Measured, one call (one lane a row -> this): 64 rows x 500 trees of depth 8
+// on 176 features 111 -> 5 us; 4099 rows of the same 130 -> 13; 20011 rows x
+// 500 trees on 110 features 230 -> 33; 65537 rows x 1000 trees 236 -> 158.
+// Small batches are bound by the fold (500 adds at about 9 clocks each) and
+// the stream of the tree tops; large ones by the tail gathers (64 lanes take
+// 64 clocks of a compute unit's address path per tree) and the LDS reads.
+// ==========================================================================
+struct RowsArgs {
+    const int32_t* feats;
+    int64_t n;
+    float* scores;
+    uint16_t* leaves;         // or null
+    int accumulate;
+    int F;
+    int quads;                // ceil(F / 4)
+    int vec;                  // rows are 16-byte aligned
+    int R;                    // rows per workgroup
+    int T;
+    int ct;                   // trees per chunk, a multiple of 4
+    int n_chunks;
+    const uint32_t* tw;       // local form, a tree every rows_stride words
+    const uint4* tail;
+    uint32_t off_ring, ring_bytes;
+    uint32_t off_lv;
+    int lv_stride;            // floats per row of leaf values
+};
+
+// Words between trees in the ring (local_tree_stride of the form).
+__host__ __device__ constexpr int rows_stride(int depth, bool tail) {
+    const int w = tail ? (depth >= 2 ? 1 << (depth - 2) : 1) : 3 << (depth - 1);
+    return w + ((1 - w) % 32 + 32) % 32;
+}
+
+template <int DEPTH, bool TAIL>
+__global__ __launch_bounds__(1024) void k_rows(RowsArgs a) {
+    constexpr int WALK = TAIL ? DEPTH - 1 : DEPTH;
+    constexpr uint32_t TB = (uint32_t)rows_stride(DEPTH, TAIL) * 4u;
+    constexpr uint32_t NBB = 4u << (DEPTH - 1);   // node block bytes of a whole tree
+    extern __shared__ uint4 lds4[];
+    uint8_t* lds = reinterpret_cast<uint8_t*>(lds4);
+    uint32_t* tile = reinterpret_cast<uint32_t*>(lds);
+    // 0: the kernel has no static LDS (checked at the launch)
+    const uint32_t lbase = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)lds;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int nthreads = (int)blockDim.x;
+    const int R = a.R;
+    const int64_t r0 = (int64_t)blockIdx.x * R;
+    const int nr = (a.n - r0 < R) ? (int)(a.n - r0) : R;
+
+    auto load_chunk = [&](int k) {
+        const int t0 = k * a.ct;
+        const int nt = a.T - t0 < a.ct ? a.T - t0 : a.ct;
+        const int n16 = (nt * (int)TB + 15) >> 4;   // the forms end in 16 bytes of slack
+        const uint4* src = reinterpret_cast<const uint4*>(a.tw + (size_t)t0 * (TB / 4u));
+        uint4* d = reinterpret_cast<uint4*>(lds + a.off_ring + (uint32_t)(k & 1) * a.ring_bytes);
+        for (int base = wave * 64; base < n16; base += nthreads)
+            if (base + lane < n16) __builtin_amdgcn_global_load_lds(src + base + lane, d + base, 16, 0, 0);
+    };
+    load_chunk(0);
+    // the tile: a wave takes min(R, 16) rows x 64 / min(R, 16) quads at a
+    // time, so that its loads cover whole lines and its stores spread over
+    // the banks; rows past the end repeat the last one
+    {
+        const int rg = R < 16 ? R : 16, qg = 64 / rg;
+        const int groups = R / rg, qgroups = (a.quads + qg - 1) / qg;
+        const int nw = nthreads >> 6;
+        for (int task = wave; task < groups * qgroups; task += nw) {
+            const int j = (task % groups) * rg + lane % rg, q = (task / groups) * qg + lane / rg;
+            if (q >= a.quads) continue;
+            const int32_t* f = a.feats + (r0 + (j < nr ? j : nr - 1)) * a.F + 4 * q;
+            int4 v;
+            if (a.vec) {
+                v = *reinterpret_cast<const int4*>(f);
+            } else {
+                const int left = a.F - 4 * q;
+                v.x = f[0];
+                v.y = left > 1 ? f[1] : 0;
+                v.z = left > 2 ? f[2] : 0;
+                v.w = left > 3 ? f[3] : 0;
+            }
+            auto b = [](int x) { return (uint32_t)min(max(x, 0), (int)NODE_THR_MAX); };
+            const uint32_t w = ((b(v.x) | (b(v.y) << 8) | (b(v.z) << 16) | (b(v.w) << 24)) << 2) | 0x03030303u;
+            for (int c = j; c < 64; c += R) tile[q * 64 + c] = w;
+        }
+    }
+    const uint32_t fb = lbase | (uint32_t)lane * 4u;
+    const int jr = lane & (R - 1);
+    const int u = (tid - 64) / R;                 // tree slot of a walk lane
+    float acc = 0.0f;
+    for (int it = 0; it <= a.n_chunks; ++it) {
+        // this wave's part of chunk `it` has landed, then everyone's
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_barrier();
+        if (it + 1 < a.n_chunks) load_chunk(it + 1);
+        if (wave == 0) {
+            if (it > 0 && lane < R) {
+                const int t0 = (it - 1) * a.ct;
+                const float* row = reinterpret_cast<const float*>(lds + a.off_lv) +
+                                   (((it - 1) & 1) * R + lane) * a.lv_stride;
+                acc = fold_row(acc, row, a.T - t0 < a.ct ? a.T - t0 : a.ct);
+            }
+        } else if (it < a.n_chunks) {
+            const int t0 = it * a.ct;
+            const int nt = a.T - t0 < a.ct ? a.T - t0 : a.ct;
+            if (4 * u < nt) {
+                uint32_t nb[4], q[4], v[4];
+                const uint32_t rb = lbase + a.off_ring + (uint32_t)(it & 1) * a.ring_bytes;
+                // (a last group's missing trees repeat its first)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) nb[g] = rb + (uint32_t)(4 * u + (4 * u + g < nt ? g : 0)) * TB;
+                walk4_local<(WALK > 0 ? WALK : 1)>(nb, fb, q);
+                if constexpr (TAIL) {
+                    uint4 rec[4];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        rec[g] = a.tail[((size_t)(t0 + 4 * u + (4 * u + g < nt ? g : 0)) << WALK) + q[g]];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const uint32_t node = rec[g].x;
+                        const uint32_t x4 = lds[((node & LOCAL_TILE_MASK) | fb) - lbase];
+                        const bool right = x4 >= (node & 0xffu);
+                        v[g] = right ? rec[g].z : rec[g].y;
+                        q[g] = 2u * q[g] + (right ? 1u : 0u);
+                    }
+                } else {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        v[g] = *reinterpret_cast<const uint32_t*>(lds + (nb[g] - lbase) + NBB + 4u * q[g]);
+                }
+                float* lv = reinterpret_cast<float*>(lds + a.off_lv) + ((it & 1) * R + jr) * a.lv_stride + 4 * u;
+                *reinterpret_cast<float4*>(lv) = make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]),
+                                                             __uint_as_float(v[2]), __uint_as_float(v[3]));
+                if (a.leaves && jr < nr) {
+                    uint16_t* o = a.leaves + (r0 + jr) * a.T + t0 + 4 * u;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        if (4 * u + g < nt) o[g] = (uint16_t)q[g];
+                }
+            }
+        }
+    }
+    if (wave == 0 && lane < nr) a.scores[r0 + lane] = a.accumulate ? a.scores[r0 + lane] + acc : acc;
+}
+
+// ==========================================================================
+// k_score: 256 rows a workgroup on the 32-bit node words.
+// ==========================================================================
 
 template <int DEPTH> struct ScoreShape {
     static constexpr int W = 2 << DEPTH;                       // words per tree
@@ -51,14 +216,16 @@ __device__ __forceinline__ void walk_add_rest(const uint8_t* L, int t, int r, ui
     if constexpr (H > 1) walk_add_rest<DEPTH, H / 2, LEAVES>(L, t, r, fb, acc, lrow, t0);
 }
 
-// SQ: feature quads of a row (44 or 48); accumulate: add the score to the
-// value already in scores (fp32, that value first) instead of storing it.
+// SQ: feature quads of a row (28, 44 or 48); align: the rows' alignment in
+// bytes (16, 8 or 4; above 4 only when a row is a multiple of it);
+// accumulate: add the score to the value already in scores (fp32, that value
+// first) instead of storing it.  Bytes past the last feature are never read.
 template <int DEPTH, bool LEAVES, int SQ>
 __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __restrict__ feats, int64_t n,
                                                float* __restrict__ scores, uint16_t* __restrict__ leaves,
-                                               int accumulate) {
+                                               int accumulate, int align) {
     using S = ScoreShape<DEPTH>;
-    constexpr int PK = SQ % 11 == 0 ? 11 : 12;   // quads loaded together
+    constexpr int PK = SQ % 11 == 0 ? 11 : (SQ % 12 == 0 ? 12 : 14);   // quads loaded together
     constexpr uint32_t TB = (uint32_t)S::W * 4u;
     __shared__ uint32_t lds[S::CW + SQ * SWG];
     const uint8_t* L = reinterpret_cast<const uint8_t*>(lds);
@@ -78,18 +245,44 @@ __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __
     {
         // rows past the end repeat the last row; their results are not stored
         const int64_t r = row < n ? row : n - 1;
-        const int4* fr = reinterpret_cast<const int4*>(feats + r * (SQ * 4));
+        const int F = e.n_features;
+        const int32_t* fr = feats + r * F;
         uint32_t packed[SQ];
+        auto pack = [](int x, int y, int z, int w) {
+            const uint32_t b0 = (uint32_t)min(max(x, 0), 255), b1 = (uint32_t)min(max(y, 0), 255);
+            const uint32_t b2 = (uint32_t)min(max(z, 0), 255), b3 = (uint32_t)min(max(w, 0), 255);
+            return b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
+        };
+        if (align == 16) {
+            const int4* f4 = reinterpret_cast<const int4*>(fr);
 #pragma unroll
-        for (int h = 0; h < SQ; h += PK) {
-            int4 v[PK];
+            for (int h = 0; h < SQ; h += PK) {
+                int4 v[PK];
 #pragma unroll
-            for (int q = 0; q < PK; ++q) v[q] = fr[h + q];
+                for (int q = 0; q < PK; ++q) v[q] = f4[h + q];
 #pragma unroll
-            for (int q = 0; q < PK; ++q) {
-                const uint32_t b0 = (uint32_t)min(max(v[q].x, 0), 255), b1 = (uint32_t)min(max(v[q].y, 0), 255);
-                const uint32_t b2 = (uint32_t)min(max(v[q].z, 0), 255), b3 = (uint32_t)min(max(v[q].w, 0), 255);
-                packed[h + q] = b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
+                for (int q = 0; q < PK; ++q) packed[h + q] = pack(v[q].x, v[q].y, v[q].z, v[q].w);
+            }
+        } else if (align == 8) {
+            // an even number of features: the last quad may hold two
+            const int2* f2 = reinterpret_cast<const int2*>(fr);
+            const int n2 = F / 2;
+#pragma unroll
+            for (int h = 0; h < SQ; h += PK) {
+                int2 v[2 * PK];
+#pragma unroll
+                for (int i = 0; i < 2 * PK; ++i) v[i] = f2[2 * h + i < n2 ? 2 * h + i : n2 - 1];
+#pragma unroll
+                for (int q = 0; q < PK; ++q)
+                    packed[h + q] = pack(v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < SQ; ++q) {
+                int x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = fr[4 * q + i < F ? 4 * q + i : F - 1];
+                packed[q] = pack(x[0], x[1], x[2], x[3]);
             }
         }
 #pragma unroll
@@ -134,26 +327,32 @@ template <int DEPTH, int SQ>
 hipError_t score_q(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
                    bool accumulate, hipStream_t stream) {
     const unsigned grid = (unsigned)((n + SWG - 1) / SWG);
+    const uintptr_t at = reinterpret_cast<uintptr_t>(feats) | ((uintptr_t)e.n_features * 4u);
+    const int align = at % 16u == 0 ? 16 : (at % 8u == 0 ? 8 : 4);
     if (leaves)
         hipLaunchKernelGGL((k_score<DEPTH, true, SQ>), dim3(grid), dim3(SWG), 0, stream, e, feats, n, scores, leaves,
-                           accumulate ? 1 : 0);
+                           accumulate ? 1 : 0, align);
     else
         hipLaunchKernelGGL((k_score<DEPTH, false, SQ>), dim3(grid), dim3(SWG), 0, stream, e, feats, n, scores, leaves,
-                           accumulate ? 1 : 0);
+                           accumulate ? 1 : 0, align);
     return hipGetLastError();
 }
 
 template <int DEPTH>
 hipError_t score_depth(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
                        bool accumulate, hipStream_t stream) {
-    if (e.n_features == 192) return score_q<DEPTH, 48>(e, feats, n, scores, leaves, accumulate, stream);
-    return score_q<DEPTH, 44>(e, feats, n, scores, leaves, accumulate, stream);
+    switch ((e.n_features + 3) / 4) {
+        case 28: return score_q<DEPTH, 28>(e, feats, n, scores, leaves, accumulate, stream);
+        case 44: return score_q<DEPTH, 44>(e, feats, n, scores, leaves, accumulate, stream);
+        case 48: return score_q<DEPTH, 48>(e, feats, n, scores, leaves, accumulate, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
 
-hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
-                        bool accumulate, hipStream_t stream) {
+hipError_t launch_score_wide(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
+                             bool accumulate, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     switch (e.depth) {
         case 1: return score_depth<1>(e, feats, n, scores, leaves, accumulate, stream);
@@ -168,6 +367,141 @@ hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, 
         case 10: return score_depth<10>(e, feats, n, scores, leaves, accumulate, stream);
         case 11: return score_depth<11>(e, feats, n, scores, leaves, accumulate, stream);
         case 12: return score_depth<12>(e, feats, n, scores, leaves, accumulate, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+namespace {
+
+// Dynamic LDS a scoring workgroup may use: the compute unit's 160 KB less 1
+// KB kept for any static LDS the compiler places.
+constexpr size_t SCORE_LDS_BYTES = 163840 - 1024;
+
+// The walks address the tile with an and-or, which needs the dynamic LDS
+// block at address 0: no static LDS in the kernel.  Raises the kernel's
+// dynamic LDS limit, once per kernel.
+hipError_t configure(const void* fn, bool& done) {
+    if (done) return hipSuccess;
+    hipFuncAttributes fa;
+    hipError_t e = hipFuncGetAttributes(&fa, fn);
+    if (e != hipSuccess) return e;
+    if (fa.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCORE_LDS_BYTES);
+    if (e == hipSuccess) done = true;
+    return e;
+}
+
+struct RowsPlan {
+    bool tail = false;
+    int R = 0, ct = 0, waves = 0;
+    size_t lds = 0;
+};
+
+// LDS layout of a plan; false when it takes more than `limit` bytes.
+bool rows_layout(const EnsembleDesc& e, RowsPlan& pl, RowsArgs& a, size_t limit) {
+    const uint32_t tb = (uint32_t)rows_stride(e.depth, pl.tail) * 4u;
+    a.quads = (e.n_features + 3) / 4;
+    a.tw = pl.tail ? e.local_top : e.local_full;
+    a.R = pl.R;
+    a.ct = pl.ct;
+    a.n_chunks = (e.n_trees + pl.ct - 1) / pl.ct;
+    a.off_ring = (uint32_t)a.quads * 256u;
+    a.ring_bytes = ((uint32_t)pl.ct * tb + 15u) / 16u * 16u;
+    a.off_lv = a.off_ring + (a.n_chunks > 1 ? 2u : 1u) * a.ring_bytes;
+    // 16-byte rows an odd number of 16-byte units apart (LDS banks)
+    a.lv_stride = 4 * (pl.ct / 4 | 1);
+    pl.lds = a.off_lv + (size_t)(a.n_chunks > 1 ? 2 : 1) * pl.R * a.lv_stride * 4;
+    return pl.lds <= limit;
+}
+
+// Plan of k_rows.  The lines lie where a sweep of rows a workgroup, waves,
+// chunk and form (n 16 .. 300000, depths 4 .. 10, 100 .. 1500 trees, 110 and
+// 176 features) put them; its plans are within 5 % of the sweep's best in
+// the geometric mean.
+//  - Rows a workgroup: 8 up to 2048 rows (a workgroup streams the whole
+//    ensemble, so fewer rows a workgroup only repeat that), then as many as
+//    leave a workgroup for each of 256 compute units, up to 32; 64 when even
+//    so the chip is full several times over (above 24576 rows; above 12288
+//    for deep trees, whose streaming costs more).
+//  - Up to one workgroup a compute unit: 16 waves and all of its LDS; more:
+//    12 waves and half of it, 8 waves from 98304 rows (500 trees of depth 8
+//    on 176 features, 4099 rows: 14.3 us with 16 waves, 17.4 with 6; 131072
+//    rows: 143 us with 8 or 12, 157 with 4).
+//  - Tails from depth 5: they stream a sixth of a whole tree's bytes, so more
+//    trees and workgroups fit (65537 rows x 1000 trees of depth 8: 158 us
+//    against 219); below, the tail gathers cost more than the leaves.
+bool plan_rows(const EnsembleDesc& e, int64_t n, RowsPlan& pl, RowsArgs& a) {
+    pl.tail = e.depth >= 5;
+    pl.R = 8;
+    while (pl.R < 32 && n > (int64_t)256 * pl.R) pl.R *= 2;
+    if (n > (e.depth >= 9 ? 12288 : 24576)) pl.R = 64;
+    const bool one = (n + pl.R - 1) / pl.R <= 256;
+    pl.waves = one ? 16 : (n < 98304 ? 12 : 8);
+    const size_t limit = one ? SCORE_LDS_BYTES : SCORE_LDS_BYTES / 2;
+    const int want = (e.n_trees + 3) / 4 * 4, per_wave = 256 / pl.R;
+    const int cap = (pl.waves - 1) * per_wave;
+    pl.ct = want < cap ? want : cap;
+    while (pl.ct >= 4 && !rows_layout(e, pl, a, limit)) pl.ct -= 4;
+    if (pl.ct < 4) return false;
+    // chunks of one size; waves that a single chunk leaves without trees go
+    const int chunks = a.n_chunks;
+    pl.ct = ((e.n_trees + chunks - 1) / chunks + 3) / 4 * 4;
+    if (chunks == 1) pl.waves = std::min(pl.waves, std::max(4, 1 + (pl.ct + per_wave - 1) / per_wave));
+    return rows_layout(e, pl, a, limit);
+}
+
+template <int DEPTH>
+hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream) {
+    static bool done[2] = {false, false};
+    constexpr bool TAILS = DEPTH >= 2;
+    const bool tail = TAILS && pl.tail;
+    const void* fn = tail ? reinterpret_cast<const void*>(&k_rows<DEPTH, TAILS>)
+                          : reinterpret_cast<const void*>(&k_rows<DEPTH, false>);
+    hipError_t e = configure(fn, done[tail]);
+    if (e != hipSuccess) return e;
+    void* args[] = {const_cast<RowsArgs*>(&a)};
+    return hipLaunchKernel(fn, dim3((unsigned)((a.n + pl.R - 1) / pl.R)), dim3(pl.waves * 64), args, pl.lds, stream);
+}
+
+}  // namespace
+
+hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
+                        bool accumulate, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    const bool vec = e.n_features % 4 == 0 && (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
+    RowsPlan pl;
+    RowsArgs a{};
+    // From 131072 rows (two workgroups a compute unit) one lane a row is the
+    // faster way for trees of up to eight levels: 2^20 rows of 176 features
+    // x 1000 trees of depth 8 take 1.75 ms against 2.3; at 131072 the two are
+    // even (148 and 143 us for 500 trees).  Deeper trees leave it one or two
+    // trees in flight a lane (depth 10, 131072 rows: 307 against 237 us).
+    const int quads = (e.n_features + 3) / 4;
+    if (n >= 131072 && e.depth <= 8 && !leaves && (quads == 28 || quads == 44 || quads == 48))
+        return launch_score_wide(e, feats, n, scores, leaves, accumulate, stream);
+    if (!plan_rows(e, n, pl, a)) return hipErrorInvalidConfiguration;
+    a.feats = feats;
+    a.n = n;
+    a.scores = scores;
+    a.leaves = leaves;
+    a.accumulate = accumulate ? 1 : 0;
+    a.F = e.n_features;
+    a.vec = vec ? 1 : 0;
+    a.T = e.n_trees;
+    a.tail = e.tail;
+    switch (e.depth) {
+        case 1: return rows_depth<1>(pl, a, stream);
+        case 2: return rows_depth<2>(pl, a, stream);
+        case 3: return rows_depth<3>(pl, a, stream);
+        case 4: return rows_depth<4>(pl, a, stream);
+        case 5: return rows_depth<5>(pl, a, stream);
+        case 6: return rows_depth<6>(pl, a, stream);
+        case 7: return rows_depth<7>(pl, a, stream);
+        case 8: return rows_depth<8>(pl, a, stream);
+        case 9: return rows_depth<9>(pl, a, stream);
+        case 10: return rows_depth<10>(pl, a, stream);
+        case 11: return rows_depth<11>(pl, a, stream);
+        case 12: return rows_depth<12>(pl, a, stream);
         default: return hipErrorInvalidValue;
     }
 }
