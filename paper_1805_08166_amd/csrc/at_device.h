@@ -122,8 +122,9 @@ __device__ __forceinline__ void unpack_split(uint64_t w, uint32_t (&f)[4]) {
 // count (the product of every factor, below 2^31 for any space) divided by
 // bottom-up, the quotient's bitlen taken without a division.  PER = 24 gives
 // the full rows with the annotation one-hot: ANN_KINDS columns, 1 at the
-// loop's annotation id, 0 elsewhere.
-template <int TMPL, int PER = 11, class Emit>
+// loop's annotation id, 0 elsewhere.  Only loops LO .. HI-1 are emitted (the
+// loops inside them take part in the products alone).
+template <int TMPL, int PER = 11, int LO = 0, int HI = Nest<TMPL>::L, class Emit>
 __device__ __forceinline__ void nest_features(const SpaceDesc& sd, const uint32_t (&fac)[6][4], const AnnKnobs& ak,
                                               Emit&& emit) {
     static_assert(PER == 11 || PER == 13 || PER == 24, "loop-context rows, full rows or one-hot rows");
@@ -141,7 +142,7 @@ __device__ __forceinline__ void nest_features(const SpaceDesc& sd, const uint32_
             for (int l = 0; l < 4; ++l) total *= fac[a][l];
     }
 #pragma unroll
-    for (int p = N::L - 1; p >= 0; --p) {
+    for (int p = N::L - 1; p >= LO; --p) {
         uint32_t ext, strd[3];
         if (N::axis[p] == FUSED) {
             const int l = N::level[p];
@@ -161,6 +162,7 @@ __device__ __forceinline__ void nest_features(const SpaceDesc& sd, const uint32_
             range[a] *= ext;
         }
         bottom_up *= ext;
+        if (p >= HI) continue;
         uint32_t t[3];
         N::touched(range, S, t);
         const uint32_t ann = annotation_of<TMPL>(p, bottom_up, ak.unroll_max, ak.unroll_id, ak.vec, ak.vth);

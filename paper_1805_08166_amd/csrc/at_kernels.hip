@@ -17,91 +17,171 @@ namespace {
 using namespace dev;
 
 // ==========================================================================
-// Feature extraction: one configuration per lane.  Rows are built as signed
-// bytes in LDS (row stride with an odd dword count so the per-lane byte
-// writes spread over the banks) and then written out as int32 with
-// consecutive lanes covering consecutive 16-byte pieces of the block, so the
-// HBM stores are fully coalesced.
+// Feature extraction.  A workgroup of four waves makes the rows of 64
+// configurations, lane r of every wave configuration r: the waves share out
+// the knobs when the indices are decoded (split factors and annotation
+// knobs go through LDS), then the loops of the nest (a wave's loops are
+// known at compile time, and the products over the loops inside them are
+// cheap), and the finished rows, signed bytes in LDS, leave as int32 with
+// consecutive lanes covering consecutive 16-byte pieces of the block.
+//
+// Bound by HBM writes at large sizes and by its own latency at small ones.
+// One configuration a lane and 256 a workgroup left both a longer serial
+// chain and, with up to 99 KB of LDS a workgroup, too few workgroups to keep
+// the stores going: 200003 conv2d rows took 33.8 us in the 208-column form
+// and 75.7 in the 384-column one against 29.2 and 51.7 (5.7 and 5.9 TB/s);
+// 2^20 rows of 176 take 146 us either way, the rate of sustained writes.
+// Non-temporal stores measured 62 us on the 384-column rows.
 // ==========================================================================
+constexpr int ROWS = 64;               // configurations per workgroup
+constexpr int WAVES = WG / 64;
+
 // PER columns per loop: 11 (loop-context rows), 13 (full Appendix A.2 rows
-// with top-down and bottom-up) or 24 (full rows with a one-hot annotation)
+// with top-down and bottom-up) or 24 (full rows with a one-hot annotation).
+// A row in LDS takes RS bytes: an odd number of dwords, so that the lanes'
+// stores spread over the banks, or, when its length is no multiple of four,
+// just its F bytes, so that the block is one flat byte array.
 template <int TMPL, int PER = 11>
 struct RowLayout {
     static constexpr int F = Nest<TMPL>::L * PER;
-    static constexpr int RS = ((F + 3) / 4 % 2 == 1) ? ((F + 3) / 4) * 4 : ((F + 3) / 4 + 1) * 4;
+    static constexpr bool FLAT = F % 4 != 0;
+    static constexpr int RS = FLAT ? F : (F / 4 | 1) * 4;
 };
 
-template <int TMPL, bool VEC, int PER = 11>
-__global__ __launch_bounds__(WG) void k_extract(SpaceDesc sd, const uint64_t* __restrict__ factors,
-                                                const uint64_t* __restrict__ cfgs, int64_t n,
-                                                int32_t* __restrict__ feats,
-                                                unsigned long long* __restrict__ n_bad) {
-    constexpr int F = RowLayout<TMPL, PER>::F;
-    constexpr int RS = RowLayout<TMPL, PER>::RS;
-    __shared__ int8_t rows[WG * RS];
-    const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * WG;
-    const int64_t row = base + tid;
-    int8_t* my = rows + tid * RS;
-    if (row < n) {
-        const uint64_t cfg = cfgs[row];
-        if (cfg >= sd.n_configs) {
-            for (int f = 0; f < F; ++f) my[f] = -1;
-            atomicAdd(n_bad, 1ull);
-        } else {
-            // mixed radix, knob 0 most significant; indices fit 32 bits
-            uint32_t rest = (uint32_t)cfg;
-            uint32_t kv[MAX_KNOBS];
-#pragma unroll
-            for (int j = MAX_KNOBS - 1; j >= 0; --j) {
-                if (j < sd.n_knobs) {
-                    const uint32_t sz = sd.knob_size[j];
-                    const uint32_t q = rest / sz;
-                    kv[j] = rest - q * sz;
-                    rest = q;
-                } else {
-                    kv[j] = 0u;
-                }
-            }
-            uint32_t fac[6][4];
-            gather_factors<TMPL>(sd, factors, kv, fac);
-            nest_features<TMPL, PER>(sd, fac, ann_knobs_of<TMPL>(sd, kv),
-                                     [&](int f, uint32_t v) { my[f] = (int8_t)v; });
-        }
+// Split factors and annotation knobs of a workgroup's configurations.
+struct Decoded {
+    uint64_t fac[MAX_AXES][ROWS];
+    uint8_t ann[ROWS][4];              // auto_unroll_max_step, unroll_explicit, vectorize, vthread
+};
+
+// Decodes configuration base + lane (mixed radix, knob 0 most significant;
+// indices and weights fit 32 bits), wave w taking knobs w, w + 4, ....
+// Returns whether the lane's index is out of range (decoded as index 0).
+template <int TMPL>
+__device__ __forceinline__ bool decode_rows(const SpaceDesc& sd, const uint64_t* __restrict__ factors,
+                                            const uint64_t* __restrict__ cfgs, int64_t base, int64_t n, int wave,
+                                            int lane, Decoded& s) {
+    constexpr int A = (TMPL == AT_TMPL_GEMM) ? 3 : 6;
+    const int64_t row = base + lane < n ? base + lane : n - 1;
+    const uint64_t cfg64 = cfgs[row];
+    const bool bad = cfg64 >= sd.n_configs;
+    const uint32_t cfg = bad ? 0u : (uint32_t)cfg64;
+    for (int j = wave; j < sd.n_knobs; j += WAVES) {
+        const uint32_t rad = (uint32_t)sd.radix[j], size = sd.knob_size[j];
+        const uint32_t q = cfg / rad;
+        const uint32_t kv = q - q / size * size;
+        if (j < A) s.fac[j][lane] = factors[sd.split_off[j] + kv];
+        else s.ann[lane][j - A] = (uint8_t)kv;
     }
-    __syncthreads();
-    const int64_t rows_here = (n - base < WG) ? (n - base) : WG;
-    const int total = (int)rows_here * F;
-    int32_t* out = feats + base * F;
-    if (VEC) {
-        // F % 4 == 0: each thread moves 4 consecutive features of one row
-        for (int g = tid; g < total / 4; g += WG) {
-            const int e = g * 4;
-            const int r = e / F, c = e - r * F;
-            const int w = *reinterpret_cast<const int*>(rows + r * RS + c);
-            int4 v;
-            v.x = (int)(int8_t)(w & 0xff);
-            v.y = (int)(int8_t)((w >> 8) & 0xff);
-            v.z = (int)(int8_t)((w >> 16) & 0xff);
-            v.w = (int)(int8_t)((w >> 24) & 0xff);
-            *reinterpret_cast<int4*>(out + e) = v;
-        }
+    return bad;
+}
+
+// Factors and annotation knobs of row r.
+template <int TMPL>
+__device__ __forceinline__ AnnKnobs decoded_row(const SpaceDesc& sd, const Decoded& s, int r, uint32_t (&fac)[6][4]) {
+    constexpr int A = (TMPL == AT_TMPL_GEMM) ? 3 : 6;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        if (a < A) unpack_split(s.fac[a][r], fac[a]);
+        else fac[a][0] = fac[a][1] = fac[a][2] = fac[a][3] = 1u;
+    }
+    uint32_t kv[MAX_KNOBS];
+#pragma unroll
+    for (int j = 0; j < MAX_KNOBS; ++j) kv[j] = (j >= A && j < A + 4) ? s.ann[r][j >= A && j < A + 4 ? j - A : 0] : 0u;
+    return ann_knobs_of<TMPL>(sd, kv);
+}
+
+// Loops LO .. HI-1 of a row into its place in LDS.
+template <int TMPL, int PER, int LO, int HI>
+__device__ __forceinline__ void emit_loops(const SpaceDesc& sd, const uint32_t (&fac)[6][4], const AnnKnobs& ak,
+                                           uint8_t* my) {
+    using RL = RowLayout<TMPL, PER>;
+    if constexpr (RL::FLAT) {
+        nest_features<TMPL, PER, LO, HI>(sd, fac, ak, [&](int f, uint32_t v) { my[f] = (uint8_t)v; });
     } else {
-        for (int e = tid; e < total; e += WG) {
-            const int r = e / F, c = e - r * F;
-            out[e] = (int32_t)rows[r * RS + c];
-        }
+        static_assert(LO * PER % 4 == 0 && HI * PER % 4 == 0, "whole dwords a wave");
+        constexpr int F0 = LO * PER, NW = (HI - LO) * PER / 4;
+        uint32_t w[NW];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) w[i] = 0u;
+        nest_features<TMPL, PER, LO, HI>(sd, fac, ak,
+                                         [&](int f, uint32_t v) { w[(f - F0) >> 2] |= v << (8 * ((f - F0) & 3)); });
+        uint32_t* d = reinterpret_cast<uint32_t*>(my + F0);
+#pragma unroll
+        for (int i = 0; i < NW; ++i) d[i] = w[i];
     }
 }
 
+__device__ __forceinline__ int4 widen(uint32_t w) {
+    return make_int4((int)(int8_t)(w & 0xffu), (int)(int8_t)((w >> 8) & 0xffu), (int)(int8_t)((w >> 16) & 0xffu),
+                     (int)(int8_t)(w >> 24));
+}
+
+// The block's rows (rows_here of them, F bytes each, RS apart) to out.
+template <int F, int RS>
+__device__ __forceinline__ void store_rows(const uint8_t* rows, int32_t* __restrict__ out, int rows_here, bool vec,
+                                           int tid, int threads) {
+    const int total = rows_here * F;
+    if (vec) {
+        for (int g = tid; g < total / 4; g += threads) {
+            int at = 4 * g;
+            if constexpr (F != RS) at = g / (F / 4) * RS + g % (F / 4) * 4;
+            reinterpret_cast<int4*>(out)[g] = widen(*reinterpret_cast<const uint32_t*>(rows + at));
+        }
+        if constexpr (F % 4 != 0)
+            for (int e = total / 4 * 4 + tid; e < total; e += threads) out[e] = (int32_t)(int8_t)rows[e];
+    } else {
+        for (int e = tid; e < total; e += threads) out[e] = (int32_t)(int8_t)rows[e / F * RS + e % F];
+    }
+}
+
+// vec: feats is 16-byte aligned
+template <int TMPL, int PER>
+__global__ __launch_bounds__(WG) void k_extract(SpaceDesc sd, const uint64_t* __restrict__ factors,
+                                                const uint64_t* __restrict__ cfgs, int64_t n,
+                                                int32_t* __restrict__ feats,
+                                                unsigned long long* __restrict__ n_bad, int vec) {
+    using RL = RowLayout<TMPL, PER>;
+    constexpr int F = RL::F, RS = RL::RS, L = Nest<TMPL>::L;
+    __shared__ __attribute__((aligned(16))) uint8_t rows[ROWS * RS];
+    __shared__ Decoded s;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int64_t base = (int64_t)blockIdx.x * ROWS;
+    const int rows_here = n - base < ROWS ? (int)(n - base) : ROWS;
+    const bool bad = decode_rows<TMPL>(sd, factors, cfgs, base, n, wave, lane, s);
+    __syncthreads();
+    {
+        uint8_t* my = rows + lane * RS;
+        uint32_t fac[6][4];
+        const AnnKnobs ak = decoded_row<TMPL>(sd, s, lane, fac);
+        switch (wave) {
+            case 0: emit_loops<TMPL, PER, 0, L / 4>(sd, fac, ak, my); break;
+            case 1: emit_loops<TMPL, PER, L / 4, L / 2>(sd, fac, ak, my); break;
+            case 2: emit_loops<TMPL, PER, L / 2, L * 3 / 4>(sd, fac, ak, my); break;
+            default: emit_loops<TMPL, PER, L * 3 / 4, L>(sd, fac, ak, my); break;
+        }
+    }
+    __syncthreads();
+    // out-of-range rows: -1 throughout, counted once
+    const bool mine = bad && lane < rows_here;
+    if (__ballot(mine)) {
+        if (wave == 0 && mine) atomicAdd(n_bad, 1ull);
+        if (mine)
+            for (int f = wave; f < F; f += WAVES) rows[lane * RS + f] = 0xff;
+        __syncthreads();
+    }
+    store_rows<F, RS>(rows, feats + base * F, rows_here, vec != 0, tid, WG);
+}
+
 // ==========================================================================
-// Context relation features (Section 4; Appendix A.2), one configuration per
-// lane.  Per buffer b and t = 1..REL_T, over the loops whose sub-nest
-// touches fewer than 2^t elements of b (bitlen(touch) <= t):
+// Context relation features (Section 4; Appendix A.2).  Per buffer b and t =
+// 1..REL_T, over the loops whose sub-nest touches fewer than 2^t elements of
+// b (bitlen(touch) <= t):
 //   R[0][b][t-1] = the largest bitlen(reuse ratio),
 //   R[1][b][t-1] = the largest bitlen(top-down product of the outer lengths),
-// 0 when no loop qualifies.  The loop quantities come from nest_features; the
-// rows go through LDS as bytes (odd dword stride) to coalesced int4 stores.
+// 0 when no loop qualifies.  The workgroup makes 64 rows as k_extract does;
+// each wave's loop quantities go through LDS, then wave b < 3 makes the
+// maxima of buffer b.
 // ==========================================================================
 constexpr int REL_T = 32;
 constexpr int REL_F = 2 * 3 * REL_T;        // 192 features per row
@@ -112,104 +192,77 @@ __global__ __launch_bounds__(WG) void k_relation(SpaceDesc sd, const uint64_t* _
                                                  const uint64_t* __restrict__ cfgs, int64_t n,
                                                  int32_t* __restrict__ feats, unsigned long long* __restrict__ n_bad) {
     using N = Nest<TMPL>;
-    __shared__ int8_t rows[WG * REL_RS];
-    const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * WG;
-    const int64_t row = base + tid;
-    int8_t* my = rows + tid * REL_RS;
-    if (row < n) {
-        const uint64_t cfg = cfgs[row];
-        if (cfg >= sd.n_configs) {
-            for (int f = 0; f < REL_F; ++f) my[f] = -1;
-            atomicAdd(n_bad, 1ull);
-        } else {
-            uint32_t rest = (uint32_t)cfg;
-            uint32_t kv[MAX_KNOBS];
-#pragma unroll
-            for (int j = MAX_KNOBS - 1; j >= 0; --j) {
-                if (j < sd.n_knobs) {
-                    const uint32_t sz = sd.knob_size[j];
-                    const uint32_t q = rest / sz;
-                    kv[j] = rest - q * sz;
-                    rest = q;
-                } else {
-                    kv[j] = 0u;
-                }
-            }
-            uint32_t fac[6][4];
-            gather_factors<TMPL>(sd, factors, kv, fac);
-            // per loop: bitlen of the touch count (tc) and of the reuse ratio (ru) per buffer
-            uint32_t tc[N::L][3], ru[N::L][3];
-            nest_features<TMPL>(sd, fac, ann_knobs_of<TMPL>(sd, kv), [&](int f, uint32_t v) {
-                const int p = f / 11, c = f - p * 11;
-                if (c >= 2 && (c - 2) % 3 == 0) tc[p][(c - 2) / 3] = v;
-                if (c >= 2 && (c - 2) % 3 == 1) ru[p][(c - 2) / 3] = v;
-            });
-            // bitlen of the top-down product of each loop (outer lengths only)
-            uint32_t td[N::L];
-            uint32_t prod = 1u;
-#pragma unroll
-            for (int p = 0; p < N::L; ++p) {
-                td[p] = bitlen(prod);
-                const uint32_t e = N::axis[p] == FUSED ? fac[4][N::level[p]] * fac[5][N::level[p]]
-                                                       : fac[N::axis[p]][N::level[p]];
-                prod *= e;
-            }
-            // A sub-nest touches no fewer elements than any sub-nest inside
-            // it, so the loops a threshold t admits (bitlen(touch) <= t) are
-            // the innermost ones from some loop p* on, and each maximum is a
-            // suffix maximum (over p* and the loops inside it).  Visiting the
-            // loops from the innermost outwards, loop p writes its suffix
-            // maxima into every threshold it admits; the outermost admitted
-            // loop, p*, writes last.  Four thresholds share a word: byte j of
-            // word w is t = 4w + 1 + j, admitted when j >= bitlen(touch) - 1 - 4w.
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                constexpr int NW = REL_T / 4;
-                uint32_t w0[NW], w1[NW];
-#pragma unroll
-                for (int w = 0; w < NW; ++w) w0[w] = w1[w] = 0u;
-                uint32_t s0 = 0u, s1 = 0u;
-#pragma unroll
-                for (int p = N::L - 1; p >= 0; --p) {
-                    s0 = max(s0, ru[p][b]);
-                    s1 = max(s1, td[p]);
-                    const uint32_t b0 = s0 * 0x01010101u, b1 = s1 * 0x01010101u;
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) {
-                        const int kb = min(max((int)tc[p][b] - 1 - 4 * w, 0), 4);
-                        const uint32_t m = (uint32_t)(0xffffffffull << (8 * kb));
-                        w0[w] = (b0 & m) | (w0[w] & ~m);
-                        w1[w] = (b1 & m) | (w1[w] & ~m);
-                    }
-                }
-                // rows are dword aligned (REL_RS = 196 bytes) and so is each
-                // 32-byte block
-                uint32_t* d0 = reinterpret_cast<uint32_t*>(my + (0 * 3 + b) * REL_T);
-                uint32_t* d1 = reinterpret_cast<uint32_t*>(my + (1 * 3 + b) * REL_T);
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    d0[w] = w0[w];
-                    d1[w] = w1[w];
-                }
-            }
+    constexpr int L = N::L;
+    __shared__ __attribute__((aligned(16))) uint8_t rows[ROWS * REL_RS];
+    __shared__ Decoded s;
+    __shared__ uint8_t tc[3][L][ROWS], ru[3][L][ROWS], td[L][ROWS];   // bitlens of touch, reuse, top-down
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int64_t base = (int64_t)blockIdx.x * ROWS;
+    const int rows_here = n - base < ROWS ? (int)(n - base) : ROWS;
+    const bool bad = decode_rows<TMPL>(sd, factors, cfgs, base, n, wave, lane, s);
+    __syncthreads();
+    {
+        uint32_t fac[6][4];
+        const AnnKnobs ak = decoded_row<TMPL>(sd, s, lane, fac);
+        auto keep = [&](int f, uint32_t v) {
+            const int p = f / 13, c = f - p * 13;
+            if (c == 2) td[p][lane] = (uint8_t)v;
+            if (c >= 4 && (c - 4) % 3 == 0) tc[(c - 4) / 3][p][lane] = (uint8_t)v;
+            if (c >= 4 && (c - 4) % 3 == 1) ru[(c - 4) / 3][p][lane] = (uint8_t)v;
+        };
+        switch (wave) {
+            case 0: nest_features<TMPL, 13, 0, L / 4>(sd, fac, ak, keep); break;
+            case 1: nest_features<TMPL, 13, L / 4, L / 2>(sd, fac, ak, keep); break;
+            case 2: nest_features<TMPL, 13, L / 2, L * 3 / 4>(sd, fac, ak, keep); break;
+            default: nest_features<TMPL, 13, L * 3 / 4, L>(sd, fac, ak, keep); break;
         }
     }
     __syncthreads();
-    const int64_t rows_here = (n - base < WG) ? (n - base) : WG;
-    const int total = (int)rows_here * REL_F;
-    int32_t* out = feats + base * REL_F;
-    for (int g = tid; g < total / 4; g += WG) {
-        const int e = g * 4;
-        const int r = e / REL_F, c = e - r * REL_F;
-        const int w = *reinterpret_cast<const int*>(rows + r * REL_RS + c);
-        int4 v;
-        v.x = (int)(int8_t)(w & 0xff);
-        v.y = (int)(int8_t)((w >> 8) & 0xff);
-        v.z = (int)(int8_t)((w >> 16) & 0xff);
-        v.w = (int)(int8_t)((w >> 24) & 0xff);
-        *reinterpret_cast<int4*>(out + e) = v;
+    if (wave < 3) {
+        // A sub-nest touches no fewer elements than any sub-nest inside it, so
+        // the loops a threshold t admits (bitlen(touch) <= t) are the
+        // innermost ones from some loop p* on, and each maximum is a suffix
+        // maximum (over p* and the loops inside it).  Visiting the loops from
+        // the innermost outwards, loop p writes its suffix maxima into every
+        // threshold it admits; the outermost admitted loop, p*, writes last.
+        // Four thresholds share a word: byte j of word w is t = 4w + 1 + j,
+        // admitted when j >= bitlen(touch) - 1 - 4w.
+        const int b = wave;
+        constexpr int NW = REL_T / 4;
+        uint32_t w0[NW], w1[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) w0[w] = w1[w] = 0u;
+        uint32_t s0 = 0u, s1 = 0u;
+#pragma unroll
+        for (int p = L - 1; p >= 0; --p) {
+            s0 = max(s0, (uint32_t)ru[b][p][lane]);
+            s1 = max(s1, (uint32_t)td[p][lane]);
+            const int t = (int)tc[b][p][lane];
+            const uint32_t b0 = s0 * 0x01010101u, b1 = s1 * 0x01010101u;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int kb = min(max(t - 1 - 4 * w, 0), 4);
+                const uint32_t m = (uint32_t)(0xffffffffull << (8 * kb));
+                w0[w] = (b0 & m) | (w0[w] & ~m);
+                w1[w] = (b1 & m) | (w1[w] & ~m);
+            }
+        }
+        if (bad) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) w0[w] = w1[w] = 0xffffffffu;
+            if (b == 0 && lane < rows_here) atomicAdd(n_bad, 1ull);
+        }
+        // rows are dword aligned (REL_RS = 196 bytes) and so is each 32-byte block
+        uint32_t* d0 = reinterpret_cast<uint32_t*>(rows + lane * REL_RS + (0 * 3 + b) * REL_T);
+        uint32_t* d1 = reinterpret_cast<uint32_t*>(rows + lane * REL_RS + (1 * 3 + b) * REL_T);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            d0[w] = w0[w];
+            d1[w] = w1[w];
+        }
     }
+    __syncthreads();
+    store_rows<REL_F, REL_RS>(rows, feats + base * REL_F, rows_here, true, tid, WG);
 }
 
 // ==========================================================================
@@ -361,88 +414,53 @@ __global__ __launch_bounds__(WG) void k_feature_scan(SpaceDesc sd, const uint64_
 
 }  // namespace
 
-hipError_t launch_extract(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats,
-                          hipStream_t stream) {
+namespace {
+
+template <int PER>
+hipError_t extract_per(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    const SpaceDesc& sd = sp.descs[0];
-    const unsigned grid = (unsigned)((n + WG - 1) / WG);
+    const unsigned grid = (unsigned)((n + ROWS - 1) / ROWS);
     const uint64_t* fac = static_cast<const uint64_t*>(sp.d_factors.p);
     auto* bad = static_cast<unsigned long long*>(sp.d_errors.p);
-    const bool aligned = (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
-    if (sp.tmpl == AT_TMPL_GEMM) {
-        // 110 features per row: not a multiple of 4, scalar stores
-        hipLaunchKernelGGL((k_extract<AT_TMPL_GEMM, false>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs, n,
-                           feats, bad);
-    } else if (aligned) {
-        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, true>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs,
-                           n, feats, bad);
-    } else {
-        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, false>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs,
-                           n, feats, bad);
-    }
+    const int vec = (reinterpret_cast<uintptr_t>(feats) & 15u) == 0 ? 1 : 0;
+    if (sp.tmpl == AT_TMPL_GEMM)
+        hipLaunchKernelGGL((k_extract<AT_TMPL_GEMM, PER>), dim3(grid), dim3(WG), 0, stream, sp.descs[0], fac, cfgs, n,
+                           feats, bad, vec);
+    else
+        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, PER>), dim3(grid), dim3(WG), 0, stream, sp.descs[0], fac,
+                           cfgs, n, feats, bad, vec);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_extract(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats,
+                          hipStream_t stream) {
+    return extract_per<11>(sp, cfgs, n, feats, stream);
 }
 
 hipError_t launch_extract_full(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats,
                                hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    const SpaceDesc& sd = sp.descs[0];
-    const unsigned grid = (unsigned)((n + WG - 1) / WG);
-    const uint64_t* fac = static_cast<const uint64_t*>(sp.d_factors.p);
-    auto* bad = static_cast<unsigned long long*>(sp.d_errors.p);
-    const bool aligned = (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
-    if (sp.tmpl == AT_TMPL_GEMM) {
-        // 130 features per row: not a multiple of 4, scalar stores
-        hipLaunchKernelGGL((k_extract<AT_TMPL_GEMM, false, 13>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs, n,
-                           feats, bad);
-    } else if (aligned) {
-        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, true, 13>), dim3(grid), dim3(WG), 0, stream, sd, fac,
-                           cfgs, n, feats, bad);
-    } else {
-        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, false, 13>), dim3(grid), dim3(WG), 0, stream, sd, fac,
-                           cfgs, n, feats, bad);
-    }
-    return hipGetLastError();
+    return extract_per<13>(sp, cfgs, n, feats, stream);
 }
 
 hipError_t launch_extract_onehot(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats,
                                  hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    const SpaceDesc& sd = sp.descs[0];
-    const unsigned grid = (unsigned)((n + WG - 1) / WG);
-    const uint64_t* fac = static_cast<const uint64_t*>(sp.d_factors.p);
-    auto* bad = static_cast<unsigned long long*>(sp.d_errors.p);
-    const bool aligned = (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
-    // 240 (GEMM) and 384 (conv2d) features per row, both multiples of 4
-    if (sp.tmpl == AT_TMPL_GEMM) {
-        if (aligned)
-            hipLaunchKernelGGL((k_extract<AT_TMPL_GEMM, true, 24>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs, n,
-                               feats, bad);
-        else
-            hipLaunchKernelGGL((k_extract<AT_TMPL_GEMM, false, 24>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs,
-                               n, feats, bad);
-    } else if (aligned) {
-        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, true, 24>), dim3(grid), dim3(WG), 0, stream, sd, fac,
-                           cfgs, n, feats, bad);
-    } else {
-        hipLaunchKernelGGL((k_extract<AT_TMPL_CONV2D_NCHW, false, 24>), dim3(grid), dim3(WG), 0, stream, sd, fac,
-                           cfgs, n, feats, bad);
-    }
-    return hipGetLastError();
+    return extract_per<24>(sp, cfgs, n, feats, stream);
 }
 
 hipError_t launch_relation(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats,
                            hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    const SpaceDesc& sd = sp.descs[0];
-    const unsigned grid = (unsigned)((n + WG - 1) / WG);
+    const unsigned grid = (unsigned)((n + ROWS - 1) / ROWS);
     const uint64_t* fac = static_cast<const uint64_t*>(sp.d_factors.p);
     auto* bad = static_cast<unsigned long long*>(sp.d_errors.p);
     if (sp.tmpl == AT_TMPL_GEMM)
-        hipLaunchKernelGGL((k_relation<AT_TMPL_GEMM>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs, n, feats, bad);
-    else
-        hipLaunchKernelGGL((k_relation<AT_TMPL_CONV2D_NCHW>), dim3(grid), dim3(WG), 0, stream, sd, fac, cfgs, n,
+        hipLaunchKernelGGL((k_relation<AT_TMPL_GEMM>), dim3(grid), dim3(WG), 0, stream, sp.descs[0], fac, cfgs, n,
                            feats, bad);
+    else
+        hipLaunchKernelGGL((k_relation<AT_TMPL_CONV2D_NCHW>), dim3(grid), dim3(WG), 0, stream, sp.descs[0], fac, cfgs,
+                           n, feats, bad);
     return hipGetLastError();
 }
 
