@@ -110,13 +110,28 @@ at_status build_feature_tables(at_space_s& sp) {
     return st;
 }
 
+// Split choices as suffix products: field l the product of the factors at
+// levels l and inside (at most the axis's extent, below 2^16).
+std::vector<uint64_t> suffix_products(const std::vector<uint64_t>& factors) {
+    std::vector<uint64_t> out(factors.size());
+    for (size_t i = 0; i < factors.size(); ++i) {
+        uint64_t prod = 1, w = 0;
+        for (int l = 3; l >= 0; --l) {
+            prod *= (factors[i] >> (16 * l)) & 0xffffu;
+            w |= prod << (16 * l);
+        }
+        out[i] = w;
+    }
+    return out;
+}
+
 // LDS images of a space's members and, for a set, the image of each block
 // of STAGE_CHAINS chains (see at_space_s).
 at_status build_stage(at_space_s& sp) {
     std::vector<int> fits(sp.n_spaces, 0);
     size_t need = 0;
     for (int i = 0; i < sp.n_spaces; ++i) {
-        const size_t nf = sp.host_factors[i].size();
+        const size_t nf = sp.host_suffix[i].size();
         fits[i] = nf <= (size_t)STAGE_FAC_MAX;
         if (fits[i]) need = std::max(need, (size_t)STAGE_DESC_BYTES + nf * 8);
     }
@@ -129,7 +144,7 @@ at_status build_stage(at_space_s& sp) {
         for (int a = 0; a < d.n_axes; ++a) d.split_off[a] -= base;
         uint8_t* dst = img.data() + stride * i;
         std::memcpy(dst, &d, sizeof d);
-        std::memcpy(dst + STAGE_DESC_BYTES, sp.host_factors[i].data(), sp.host_factors[i].size() * 8);
+        std::memcpy(dst + STAGE_DESC_BYTES, sp.host_suffix[i].data(), sp.host_suffix[i].size() * 8);
     }
     sp.stage_stride = (int)stride;
     at_status st = upload(sp.d_stage, img.data(), img.size());
@@ -218,9 +233,10 @@ at_status at_space_create(int tmpl, const int64_t* shape, int nshape, at_space_t
     sp->n_spaces = 1;
     sp->descs.push_back(d);
     sp->chain_offsets = {0, 0};
-    sp->host_factors.push_back(factors);
+    sp->host_suffix.push_back(suffix_products(factors));
     int64_t offs[2] = {0, INT64_MAX};
     if ((st = upload(sp->d_descs, &d, 1)) != AT_OK || (st = upload(sp->d_factors, factors.data(), factors.size())) != AT_OK ||
+        (st = upload(sp->d_suffix, sp->host_suffix[0].data(), sp->host_suffix[0].size())) != AT_OK ||
         (st = upload(sp->d_offsets, offs, 2)) != AT_OK || (st = alloc_zero(sp->d_errors, 8)) != AT_OK ||
         (st = build_stage(*sp)) != AT_OK || (st = scan_constant_features(*sp)) != AT_OK ||
         (st = build_feature_tables(*sp)) != AT_OK) {
@@ -269,10 +285,10 @@ at_status at_spaceset_create(const at_space_t* spaces, int n, const int64_t* cha
         SpaceDesc d = spaces[i]->descs[0];
         const int32_t shift = (int32_t)all.size();
         for (int a = 0; a < d.n_axes; ++a) d.split_off[a] += shift;
-        const std::vector<uint64_t>& f = spaces[i]->host_factors[0];
+        const std::vector<uint64_t>& f = spaces[i]->host_suffix[0];
         all.insert(all.end(), f.begin(), f.end());
         sp->descs.push_back(d);
-        sp->host_factors.push_back(f);
+        sp->host_suffix.push_back(f);
     }
     sp->chain_offsets.assign(chain_offsets, chain_offsets + n + 1);
     // a feature is constant over the set when every member gives it the same
@@ -289,7 +305,7 @@ at_status at_spaceset_create(const at_space_t* spaces, int n, const int64_t* cha
     }
     at_status st;
     if ((st = upload(sp->d_descs, sp->descs.data(), sp->descs.size())) != AT_OK ||
-        (st = upload(sp->d_factors, all.data(), all.size())) != AT_OK ||
+        (st = upload(sp->d_suffix, all.data(), all.size())) != AT_OK ||
         (st = upload(sp->d_offsets, sp->chain_offsets.data(), sp->chain_offsets.size())) != AT_OK ||
         (st = alloc_zero(sp->d_errors, 8)) != AT_OK || (st = build_stage(*sp)) != AT_OK ||
         (st = build_feature_tables(*sp)) != AT_OK) {
@@ -305,6 +321,7 @@ void at_space_destroy(at_space_t space) {
     DeviceGuard g(space->device);
     release(space->d_descs);
     release(space->d_factors);
+    release(space->d_suffix);
     release(space->d_offsets);
     release(space->d_errors);
     release(space->d_stage);

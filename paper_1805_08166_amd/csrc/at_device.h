@@ -186,67 +186,144 @@ __device__ __forceinline__ void nest_features(const SpaceDesc& sd, const uint32_
     }
 }
 
-// The loop-context features of loop p alone (out[0..10]), for evaluating one
-// schedule with one lane per loop.  Same arithmetic as nest_features: the
-// running products over the loops at or inside p are formed by visiting every
-// loop from the innermost outwards and multiplying in only those with index
-// >= p; loop p's own quantities are captured when it is visited.  td, when
-// given, receives bitlen(top-down) of loop p: the product of the lengths of
-// the loops outside it, i.e. the nest's iteration count over bottom-up.
+// Per-loop tables for loop_features, two or three bits a loop in one word:
+// the outermost level of axis a at or inside loop p (levels outside p are
+// those whose loop comes before it), and loop p's axis (5 for a fused loop).
 template <int TMPL>
-__device__ __forceinline__ void loop_features(const SpaceDesc& sd, const uint32_t (&fac)[6][4], const AnnKnobs& ak,
-                                              int p, uint32_t (&out)[11], uint32_t* td = nullptr) {
+__host__ __device__ constexpr int levels_outside(int a, int p) {
     using N = Nest<TMPL>;
-    uint32_t range[6] = {1u, 1u, 1u, 1u, 1u, 1u};
-    uint32_t bottom_up = 1u, ext = 1u;
-    uint32_t strd[3] = {0u, 0u, 0u};
+    int c = 0;
+    for (int q = 0; q < p; ++q) c += (N::axis[q] == a || (N::axis[q] == FUSED && a >= 4)) ? 1 : 0;
+    return c;
+}
+template <int TMPL>
+__host__ __device__ constexpr uint32_t level_table(int a) {
+    uint32_t t = 0;
+    for (int p = 0; p < Nest<TMPL>::L; ++p) {
+        const int l = levels_outside<TMPL>(a, p);
+        t |= (uint32_t)(l < 3 ? l : 3) << (2 * p);
+    }
+    return t;
+}
+// bit p: every level of axis a lies outside loop p
+template <int TMPL>
+__host__ __device__ constexpr uint32_t outside_table(int a) {
+    uint32_t t = 0;
+    for (int p = 0; p < Nest<TMPL>::L; ++p) t |= (levels_outside<TMPL>(a, p) == 4 ? 1u : 0u) << p;
+    return t;
+}
+template <int TMPL>
+__host__ __device__ constexpr uint64_t axis_table() {
+    uint64_t t = 0;
+    for (int p = 0; p < Nest<TMPL>::L; ++p) {
+        const int a = Nest<TMPL>::axis[p] == FUSED ? 5 : Nest<TMPL>::axis[p];
+        t |= (uint64_t)a << (3 * p);
+    }
+    return t;
+}
+
+// The loop-context features of loop p alone (out[0..10]) of the configuration
+// with knob values kv, for evaluating one schedule with one lane per loop.
+// The same quantities as nest_features, from the split choices' suffix
+// products (sfx: field l of a choice is the product of its factors at levels
+// l and inside): the range of axis a at or inside loop p is the field of its
+// outermost level there, and the range strictly inside p the next field of
+// p's own axis, so every quantity is a few reads and a product of ranges
+// (below 2^16 each, so pairs multiply in 24 bits).  Walking the nest and
+// multiplying the loops up, as before, cost some 80 full 32-bit products a
+// loop, at a quarter of the other instructions' rate.  bitlen(length) is the
+// bitlen of the exact quotient of the two ranges.  td receives, when asked
+// for, bitlen(top-down): the nest's iteration count over bottom-up.
+template <int TMPL>
+__device__ __forceinline__ void loop_features(const SpaceDesc& sd, const uint64_t* __restrict__ sfx,
+                                              const uint32_t (&kv)[MAX_KNOBS], int p, uint32_t (&out)[11],
+                                              uint32_t& td, bool want_td) {
+    using N = Nest<TMPL>;
+    constexpr bool CONV = TMPL == AT_TMPL_CONV2D_NCHW;
+    constexpr int A = CONV ? 6 : 3;
+    const uint16_t* f16 = reinterpret_cast<const uint16_t*>(sfx);
+    // field index of each axis's range, and the ranges
+    uint32_t at[A], r[6] = {1u, 1u, 1u, 1u, 1u, 1u};
 #pragma unroll
-    for (int q = N::L - 1; q >= 0; --q) {
-        const bool in = q >= p, at = q == p;
-        uint32_t e, sq[3];
-        if (N::axis[q] == FUSED) {
-            const int l = N::level[q];
-            const uint32_t fy = fac[4][l], fx = fac[5][l];
-            e = fy * fx;
-#pragma unroll
-            for (int b = 0; b < 3; ++b)
-                sq[b] = (fx > 1u) ? (uint32_t)sd.coef[b][5] * range[5] : (uint32_t)sd.coef[b][4] * range[4];
-            range[4] *= in ? fy : 1u;
-            range[5] *= in ? fx : 1u;
-        } else {
-            const int a = N::axis[q];
-            e = fac[a][N::level[q]];
-#pragma unroll
-            for (int b = 0; b < 3; ++b) sq[b] = (uint32_t)sd.coef[b][a] * range[a];
-            range[a] *= in ? e : 1u;
-        }
-        bottom_up *= in ? e : 1u;
-        if (at) {
-            ext = e;
-#pragma unroll
-            for (int b = 0; b < 3; ++b) strd[b] = sq[b];
+    for (int a = 0; a < A; ++a) {
+        at[a] = 4u * ((uint32_t)sd.split_off[a] + kv[a]) + ((level_table<TMPL>(a) >> (2 * p)) & 3u);
+        r[a] = f16[at[a]];
+        if constexpr (true) {
+            constexpr auto none = [](int ax) { return outside_table<TMPL>(ax); };
+            if (none(a) != 0u) r[a] = ((none(a) >> p) & 1u) ? 1u : r[a];
         }
     }
-    uint32_t t[3];
-    N::touched(range, (uint32_t)sd.stride, t);
-    if (td) {
-        uint32_t total = 1u;
+    // loop p's own axis: its range at and strictly inside p (1 inside the
+    // innermost of four levels; both axes for a fused loop)
+    const uint32_t ax = (uint32_t)(axis_table<TMPL>() >> (3 * p)) & 7u;
+    uint32_t own = at[0], rown = r[0];
 #pragma unroll
-        for (int a = 0; a < 6; ++a)
-#pragma unroll
-            for (int l = 0; l < 4; ++l) total *= fac[a][l];
-        *td = bitlen_quot(total, bottom_up);
+    for (int a = 1; a < A; ++a) {
+        own = ax == (uint32_t)a ? at[a] : own;
+        rown = ax == (uint32_t)a ? r[a] : rown;
     }
-    out[0] = bitlen(ext);
-    out[1] = annotation_of<TMPL>(p, bottom_up, ak.unroll_max, ak.unroll_id, ak.vec, ak.vth);
+    uint32_t rin = 1u;
+    if ((own & 3u) != 3u) rin = f16[own + 1u];
+    uint32_t incl = rown, excl = rin, axs = ax, inside = rin;
+    if constexpr (CONV) {
+        const bool fused = ax == 5u;
+        const uint32_t rin4 = f16[at[4] + (fused ? 1u : 0u)];   // read by every lane, used by fused loops
+        incl = fused ? __umul24(r[4], r[5]) : rown;
+        excl = fused ? __umul24(rin4, rin) : rin;
+        // one step of a fused loop moves rx when rx has several values, else ry
+        const bool ry = fused && rown == rin;
+        axs = ry ? 4u : ax;
+        inside = ry ? rin4 : rin;
+    }
+    const uint32_t r01 = __umul24(r[0], r[1]);
+    uint32_t bottom_up, t[3], total = 1u;
+    if constexpr (CONV) {
+        const uint32_t r45 = __umul24(r[4], r[5]), r23 = __umul24(r[2], r[3]);
+        bottom_up = r01 * r23 * r45;
+        const uint32_t S = (uint32_t)sd.stride;
+        auto distinct = [&](uint32_t x, uint32_t y) {
+            return (x == 1u || y >= S) ? __umul24(x - 1u, S) + y : __umul24(x, y);
+        };
+        t[0] = r[3] * distinct(r[1], r[4]) * distinct(r[2], r[5]);
+        t[1] = __umul24(r[0], r[3]) * r45;
+        t[2] = r01 * r[2];
+    } else {
+        bottom_up = r01 * r[2];
+        t[0] = __umul24(r[2], r[0]);
+        t[1] = __umul24(r[2], r[1]);
+        t[2] = r01;
+    }
+    td = 0u;
+    if (want_td) {
+        // field 0 of any choice of an axis is its extent
+#pragma unroll
+        for (int a = 0; a < A; ++a) total *= (uint32_t)f16[4u * (uint32_t)sd.split_off[a]];
+        td = bitlen_quot(total, bottom_up);
+    }
+    out[0] = bitlen_quot(incl, excl);
+    // annotation: binding, virtual threads, vectorized, unrolled, serial
+    {
+        const AnnKnobs ak = ann_knobs_of<TMPL>(sd, kv);
+        uint64_t binds = 0;
+        uint32_t vthr = 0;
+#pragma unroll
+        for (int q = 0; q < N::L; ++q) {
+            binds |= (uint64_t)N::bind[q] << (4 * q);
+            vthr |= (N::level[q] == 2 && N::axis[q] >= 0 && N::axis[q] < N::SPATIAL ? 1u : 0u) << q;
+        }
+        const uint32_t bind = (uint32_t)(binds >> (4 * p)) & 15u;
+        uint32_t ann = (ak.unroll_max > 0u && bottom_up <= ak.unroll_max) ? ak.unroll_id : 0u;
+        if (ak.vec && p == N::L - 1) ann = ANN_VECTORIZE;
+        if (ak.vth && ((vthr >> p) & 1u)) ann = ANN_VTHREAD;
+        out[1] = bind ? bind : ann;
+    }
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
         out[2 + 3 * b] = bitlen(t[b]);
         out[3 + 3 * b] = bitlen_quot(bottom_up, t[b]);
-        out[4 + 3 * b] = bitlen(strd[b]);
+        out[4 + 3 * b] = bitlen((uint32_t)sd.coef[b][axs] * inside);
     }
 }
-
 
 // Factors of every axis for knob values kv (split knob a = axis a).
 template <int TMPL>

@@ -53,7 +53,8 @@ struct SpaceDesc {
 
 // LDS image of one space for the annealing chain kernel: the descriptor
 // with its split offsets rebased to 0 in the first STAGE_DESC_BYTES, then
-// the space's split factors (u64), at most STAGE_FAC_MAX of them.  Images
+// the suffix products of its split choices (u64), at most STAGE_FAC_MAX of
+// them.  Images
 // of a space set lie STAGE_ALIGN-multiple strides apart; the kernel copies
 // a whole stride with 16-byte direct-to-LDS moves of whole waves.
 constexpr int STAGE_DESC_BYTES = (int)((sizeof(SpaceDesc) + 15) / 16 * 16);
@@ -187,7 +188,8 @@ struct at_space_s {
     std::vector<at::SpaceDesc> descs;       // host copies
     std::vector<int64_t> chain_offsets;     // [n_spaces + 1] (sets only)
     at::DeviceBuf d_descs;                  // SpaceDesc[n_spaces]
-    at::DeviceBuf d_factors;                // uint64 split factor tables
+    at::DeviceBuf d_factors;                // uint64 split factor tables (single spaces)
+    at::DeviceBuf d_suffix;                 // the same choices as suffix products (field l: levels l and inside)
     at::DeviceBuf d_offsets;                // int64 [n_spaces + 1]
     at::DeviceBuf d_errors;                 // uint64 out-of-range counter
     // LDS images of the member spaces (stage_stride bytes apart, 0 when no
@@ -199,8 +201,8 @@ struct at_space_s {
     int stage_stride = 0;
     int stage_single = -1;
     at::DeviceBuf d_wg_space;
-    // per member space: its factor tables as host data (for building sets)
-    std::vector<std::vector<uint64_t>> host_factors;
+    // per member space: its suffix products as host data (for building sets)
+    std::vector<std::vector<uint64_t>> host_suffix;
     // Loop-context features constant over the space (set): fconst[f] is the
     // value every configuration gives feature f, 0xff when it varies; empty
     // when the space was too large to scan.

@@ -41,7 +41,7 @@ struct LocalArgs {
     const SpaceDesc* descs;
     const int64_t* offsets;
     int n_spaces;
-    const uint64_t* factors;
+    const uint64_t* suffix;   // split choices as suffix products
     uint16_t* knobs;          // [n][MAX_KNOBS] current configuration
     float* cur_score;         // [n]
     at_entry* top;            // [n][topk] best lists
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         uint32_t* ld = reinterpret_cast<uint32_t*>(&s_desc);
         for (int i = tid; i < DW; i += nthreads)
             ld[i] = (i >= SO && i < SO + MAX_AXES) ? gd[i] - (uint32_t)fac_lo : gd[i];
-        for (int i = tid; i < fac_n; i += nthreads) s_fac[i] = a.factors[fac_lo + i];
+        for (int i = tid; i < fac_n; i += nthreads) s_fac[i] = a.suffix[fac_lo + i];
     }
     // space of the owner's chain: the staged copy in LDS or the set's tables
     // in global memory.  Each use branches on
@@ -322,15 +322,13 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
     // Loop gr's features of chain j's configuration nx into row dst.
     auto eval_loop = [&](const uint32_t (&nx)[MAX_KNOBS], int j, int gr_, uint8_t* dst) {
         auto feats = [&](const SpaceDesc& sd, const uint64_t* facp) {
-            uint32_t fac[6][4];
-            gather_factors<TMPL>(sd, facp, nx, fac);
-            uint32_t f[11];
-            loop_features<TMPL>(sd, fac, ann_knobs_of<TMPL>(sd, nx), gr_, f);
+            uint32_t f[11], td;
+            loop_features<TMPL>(sd, facp, nx, gr_, f, td, false);
 #pragma unroll
             for (int i = 0; i < 11; ++i) dst[gr_ * 11 + i] = (uint8_t)f[i];
         };
         if (staged) feats(s_desc, s_fac);
-        else feats(a.descs[space_of(a.offsets, a.n_spaces, c0 + j)], a.factors);
+        else feats(a.descs[space_of(a.offsets, a.n_spaces, c0 + j)], a.suffix);
     };
     auto unpack = [](const uint32_t (&w)[MAX_KNOBS / 2], uint32_t (&nx)[MAX_KNOBS]) {
 #pragma unroll
@@ -921,7 +919,7 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     a.descs = static_cast<const SpaceDesc*>(sp.d_descs.p);
     a.offsets = static_cast<const int64_t*>(sp.d_offsets.p);
     a.n_spaces = sp.n_spaces;
-    a.factors = static_cast<const uint64_t*>(sp.d_factors.p);
+    a.suffix = static_cast<const uint64_t*>(sp.d_suffix.p);
     a.knobs = static_cast<uint16_t*>(ch.d_knobs.p);
     a.cur_score = static_cast<float*>(ch.d_score.p);
     a.top = static_cast<at_entry*>(ch.d_top.p);

@@ -38,9 +38,11 @@ __device__ __forceinline__ int64_t v_index(int64_t c, int t, int groups) {
     return ((((c >> 4) * groups + (t >> 2)) << 6) + ((c & 15) << 2) + (t & 3));
 }
 
-// Chain-kernel workgroups have 256 or 512 threads (template argument
-// CHAIN_WG): wave 0 folds, the others build the next candidates (see
-// launch_sa_tp for the choice).
+// Chain-kernel workgroups: wave 0 folds, the others build the next
+// candidates.  (Eight waves measured no faster on either side of the fold's
+// length: twelve conv2d workloads, 1000 trees, 9.8 us a launch against 9.6;
+// C12, 2000 trees, 15.6 against 15.0.)
+constexpr int CHAIN_WG = 256;
 constexpr int CPW = 16;                 // chains per chain-kernel workgroup
 static_assert(CPW == 16 && CPW == STAGE_CHAINS, "a chain-kernel workgroup reads one 16-chain block of V");
 constexpr int FOLD_P = 32;              // 4-tree groups per fold pass: 32 x 16 chains x 16 B = 8 KB
@@ -64,8 +66,8 @@ struct ChainArgs {
     const SpaceDesc* descs;
     const int64_t* offsets;
     int n_spaces;
-    const uint64_t* factors;
-    // LDS images of the spaces (descriptor rebased, then split factors),
+    const uint64_t* suffix;   // split choices as suffix products
+    // LDS images of the spaces (descriptor rebased, then suffix products),
     // stage_stride bytes apart; the image of a workgroup's chains is
     // stage_single (one space) or wg_space[workgroup] (sets), -1 for none
     const uint8_t* stage;
@@ -100,13 +102,6 @@ struct ChainArgs {
     const float* Vg;
     int Tg;
     uint32_t* Fr;
-    // trees of the next tree launch, relocated (pf_tree_bytes each, pf_tpw
-    // a tree workgroup, pf_trees in all): the building waves bring them
-    // into their XCD's L2 before the tree kernel copies them; null: none
-    const uint8_t* pf_trees;
-    int pf_tree_bytes;
-    int pf_tpw;
-    int pf_ntrees;
     // tile layout of Fg: fq quads, position p holding loop-context feature
     // fsrc[p] (0xff: padding); fident: position p holds feature p
     const uint8_t* fsrc;
@@ -476,10 +471,8 @@ __device__ __forceinline__ void step_move(const SpaceDesc& sd, uint32_t k0, uint
 template <int TMPL>
 __device__ __forceinline__ void row_features(const SpaceDesc& sd, const uint64_t* facp, const uint32_t (&nx)[MAX_KNOBS],
                                              int l, bool want_td, uint8_t* row, uint8_t* td) {
-    uint32_t fac[6][4];
-    gather_factors<TMPL>(sd, facp, nx, fac);
-    uint32_t f[11], t = 0u;
-    loop_features<TMPL>(sd, fac, ann_knobs_of<TMPL>(sd, nx), l, f, want_td ? &t : nullptr);
+    uint32_t f[11], t;
+    loop_features<TMPL>(sd, facp, nx, l, f, t, want_td);
 #pragma unroll
     for (int i = 0; i < 11; ++i) row[l * 11 + i] = (uint8_t)f[i];
     td[l] = (uint8_t)t;
@@ -513,7 +506,7 @@ struct TpRec {
 // once the score is known the owner lanes (wave 0, lane j: chain c0 + j)
 // offer the candidate to the best list, take the Metropolis decision and
 // the rows of the candidate that follows go out.
-template <int TMPL, int CHAIN_WG>
+template <int TMPL>
 __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     using N = Nest<TMPL>;
     constexpr int L = N::L;
@@ -549,7 +542,7 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     const int ws = a.n_spaces == 1 ? a.stage_single : a.wg_space[blockIdx.x];
     const bool staged = ws >= 0;
     const SpaceDesc* s_desc = reinterpret_cast<const SpaceDesc*>(s_img);
-    const uint64_t* facp = staged ? reinterpret_cast<const uint64_t*>(s_img + STAGE_DESC_BYTES) : a.factors;
+    const uint64_t* facp = staged ? reinterpret_cast<const uint64_t*>(s_img + STAGE_DESC_BYTES) : a.suffix;
     auto desc_of = [&](int j) -> const SpaceDesc& {
         return staged ? *s_desc : a.descs[space_of(a.offsets, a.n_spaces, c0 + j)];
     };
@@ -714,40 +707,6 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
                     uint32_t nx[MAX_KNOBS];
                     unpack_pairs(mv[jo], nx);
                     row_features<TMPL>(desc_of(j), facp, nx, l, a.Fr != nullptr, frow[o][j], tdrow[o][j]);
-                }
-            }
-            if (a.pf_trees) {
-                // the next tree launch copies its trees from the L2: chain
-                // workgroup b takes half of the trees of tree workgroup
-                // 8 * (b / 16) + b % 8, which runs on the same XCD when
-                // workgroups go round the eight XCDs in turn (a wrong guess
-                // only warms another XCD's L2)
-                const int b = (int)blockIdx.x;
-                const int tw = 8 * (b / 16) + b % 8, half = (b / 8) & 1;
-                const int per = a.pf_tpw / 2 > 0 ? a.pf_tpw / 2 : 1;
-                const int first = tw * a.pf_tpw + half * per;
-                int cnt = a.pf_ntrees - first < per ? a.pf_ntrees - first : per;
-                if (half == 1 && a.pf_tpw == 1) cnt = 0;
-                if (cnt > 0) {
-                    const int64_t bytes = (int64_t)cnt * a.pf_tree_bytes;
-                    const uint8_t* src = a.pf_trees + (int64_t)first * a.pf_tree_bytes;
-                    // plain loads, all in flight before one wait: each lane
-                    // takes 16 bytes of every 1 KB line its wave covers (at most
-                    // PF_LINES lines a wave), from a valid address on every
-                    // lane, the values folded into one that is kept
-                    constexpr int PF_LINES = 12;
-                    const int nbw = CHAIN_WG / 64 - 1;
-                    uint32_t keep = 0u;
-                    uint4 v[PF_LINES];
-#pragma unroll
-                    for (int u = 0; u < PF_LINES; ++u) {
-                        int64_t off = ((int64_t)u * nbw + (wave - 1)) * 1024 + lane * 16;
-                        off = off < bytes ? off : bytes - 16;
-                        v[u] = *reinterpret_cast<const uint4*>(src + off);
-                    }
-#pragma unroll
-                    for (int u = 0; u < PF_LINES; ++u) keep ^= v[u].x;
-                    asm volatile("" ::"v"(keep));
                 }
             }
         }
@@ -1639,7 +1598,7 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
     ca.descs = static_cast<const SpaceDesc*>(sp.d_descs.p);
     ca.offsets = static_cast<const int64_t*>(sp.d_offsets.p);
     ca.n_spaces = sp.n_spaces;
-    ca.factors = static_cast<const uint64_t*>(sp.d_factors.p);
+    ca.suffix = static_cast<const uint64_t*>(sp.d_suffix.p);
     ca.stage = static_cast<const uint8_t*>(sp.d_stage.p);
     ca.stage_stride = sp.stage_stride;
     ca.stage_single = sp.stage_single;
@@ -1692,10 +1651,8 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
     }
     static bool chain_configured = false;
     if (!chain_configured) {
-        for (const void* f : {reinterpret_cast<const void*>(&k_chain<AT_TMPL_GEMM, 256>),
-                              reinterpret_cast<const void*>(&k_chain<AT_TMPL_CONV2D_NCHW, 256>),
-                              reinterpret_cast<const void*>(&k_chain<AT_TMPL_GEMM, 512>),
-                              reinterpret_cast<const void*>(&k_chain<AT_TMPL_CONV2D_NCHW, 512>)}) {
+        for (const void* f : {reinterpret_cast<const void*>(&k_chain<AT_TMPL_GEMM>),
+                              reinterpret_cast<const void*>(&k_chain<AT_TMPL_CONV2D_NCHW>)}) {
             if ((err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)(ring_bytes(true) + (size_t)CPW * KMAX * sizeof(at_entry)))) != hipSuccess)
                 return err;
@@ -1703,25 +1660,16 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
         chain_configured = true;
     }
     ch.events_used[0] = ch.events_used[1] = 0;
-    // While wave 0 folds, the other waves build both next candidates of 16
-    // chains (2 x 16 x L loop-feature tasks).  With a short fold (under 1500
-    // trees in all) that building is the longer of the two and eight waves
-    // take it (twelve conv2d workloads, 1000 trees: 14.2 -> 13.3 ms a run);
-    // with a long fold four waves leave the folding wave more of its SIMD
-    // (C12, 2000 trees: 56.6 against 57.1 ms).
-    const bool wide = e.n_trees + (eg ? eg->n_trees : 0) < 1500;
     auto chain_kernel = [&](const ChainArgs& x) -> hipError_t {
         const size_t lds = x.fin == FIN_NONE ? 0 : chain_lds;
         hipEvent_t start, stop;
         const hipError_t ev = next_events(ch, 1, start, stop);
         if (ev != hipSuccess) return ev;
-        auto kern = sp.tmpl == AT_TMPL_GEMM ? (wide ? k_chain<AT_TMPL_GEMM, 512> : k_chain<AT_TMPL_GEMM, 256>)
-                                            : (wide ? k_chain<AT_TMPL_CONV2D_NCHW, 512> : k_chain<AT_TMPL_CONV2D_NCHW, 256>);
-        const int wg = wide ? 512 : 256;
+        auto kern = sp.tmpl == AT_TMPL_GEMM ? k_chain<AT_TMPL_GEMM> : k_chain<AT_TMPL_CONV2D_NCHW>;
         if (start)
-            hipExtLaunchKernelGGL(kern, dim3(chain_grid), dim3(wg), lds, stream, start, stop, 0, x);
+            hipExtLaunchKernelGGL(kern, dim3(chain_grid), dim3(CHAIN_WG), lds, stream, start, stop, 0, x);
         else
-            hipLaunchKernelGGL(kern, dim3(chain_grid), dim3(wg), lds, stream, x);
+            hipLaunchKernelGGL(kern, dim3(chain_grid), dim3(CHAIN_WG), lds, stream, x);
         return hipGetLastError();
     };
     auto trees_kernel = [&]() -> hipError_t {
@@ -1750,15 +1698,6 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
         x.fin_step = s - 1;
         x.draw = DRAW_PROPOSE;
         x.draw_step = (uint32_t)(ch.step_abs + (uint64_t)s);
-        if (!eg && !wide) {
-            // a long fold leaves the building waves time to spare: they bring
-            // the next tree launch's trees into the L2 (with a short fold the
-            // building is the longer side and this would lengthen the step)
-            x.pf_trees = reinterpret_cast<const uint8_t*>(tl.ta.words32);
-            x.pf_tree_bytes = 8 << e.depth;
-            x.pf_tpw = tl.ta.tpw;
-            x.pf_ntrees = e.n_trees;
-        }
         if ((err = chain_kernel(x)) != hipSuccess) return err;
         if ((err = trees_kernel()) != hipSuccess) return err;
         pending = FIN_STEP;
