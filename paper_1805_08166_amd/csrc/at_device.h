@@ -325,6 +325,40 @@ __device__ __forceinline__ void loop_features(const SpaceDesc& sd, const uint64_
     }
 }
 
+// Context relation features of one buffer (thresholds t = 1 .. 32): byte t-1
+// of w0 is the largest ru(p), of w1 the largest td(p), over the loops p with
+// tc(p) <= t; tc, ru and td give the bitlens of loop p's touch count, reuse
+// ratio and top-down product.  A sub-nest touches no fewer elements than any
+// sub-nest inside it, so the loops a threshold admits are the innermost ones
+// from some loop p* on, and each maximum is a suffix maximum (over p* and
+// the loops inside it).  Visiting the loops from the innermost outwards,
+// loop p writes its suffix maxima into every threshold it admits; the
+// outermost admitted loop, p*, writes last.  Four thresholds share a word:
+// byte j of word w is t = 4w + 1 + j, admitted when j >= tc(p) - 1 - 4w.
+constexpr int REL_T = 32;
+constexpr int REL_NW = REL_T / 4;
+template <int L, class Tc, class Ru, class Td>
+__device__ __forceinline__ void relation_maxima(Tc&& tc, Ru&& ru, Td&& td, uint32_t (&w0)[REL_NW],
+                                                uint32_t (&w1)[REL_NW]) {
+#pragma unroll
+    for (int w = 0; w < REL_NW; ++w) w0[w] = w1[w] = 0u;
+    uint32_t s0 = 0u, s1 = 0u;
+#pragma unroll
+    for (int p = L - 1; p >= 0; --p) {
+        s0 = max(s0, ru(p));
+        s1 = max(s1, td(p));
+        const int t = (int)tc(p);
+        const uint32_t b0 = s0 * 0x01010101u, b1 = s1 * 0x01010101u;
+#pragma unroll
+        for (int w = 0; w < REL_NW; ++w) {
+            const int kb = min(max(t - 1 - 4 * w, 0), 4);
+            const uint32_t m = (uint32_t)(0xffffffffull << (8 * kb));
+            w0[w] = (b0 & m) | (w0[w] & ~m);
+            w1[w] = (b1 & m) | (w1[w] & ~m);
+        }
+    }
+}
+
 // Factors of every axis for knob values kv (split knob a = axis a).
 template <int TMPL>
 __device__ __forceinline__ void gather_factors(const SpaceDesc& sd, const uint64_t* __restrict__ factors,

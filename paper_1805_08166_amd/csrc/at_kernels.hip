@@ -183,8 +183,7 @@ __global__ __launch_bounds__(WG) void k_extract(SpaceDesc sd, const uint64_t* __
 // each wave's loop quantities go through LDS, then wave b < 3 makes the
 // maxima of buffer b.
 // ==========================================================================
-constexpr int REL_T = 32;
-constexpr int REL_F = 2 * 3 * REL_T;        // 192 features per row
+constexpr int REL_F = RELATION_FEATURES;
 constexpr int REL_RS = REL_F + 4;           // 49 dwords per LDS row
 
 template <int TMPL>
@@ -219,44 +218,21 @@ __global__ __launch_bounds__(WG) void k_relation(SpaceDesc sd, const uint64_t* _
     }
     __syncthreads();
     if (wave < 3) {
-        // A sub-nest touches no fewer elements than any sub-nest inside it, so
-        // the loops a threshold t admits (bitlen(touch) <= t) are the
-        // innermost ones from some loop p* on, and each maximum is a suffix
-        // maximum (over p* and the loops inside it).  Visiting the loops from
-        // the innermost outwards, loop p writes its suffix maxima into every
-        // threshold it admits; the outermost admitted loop, p*, writes last.
-        // Four thresholds share a word: byte j of word w is t = 4w + 1 + j,
-        // admitted when j >= bitlen(touch) - 1 - 4w.
         const int b = wave;
-        constexpr int NW = REL_T / 4;
-        uint32_t w0[NW], w1[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) w0[w] = w1[w] = 0u;
-        uint32_t s0 = 0u, s1 = 0u;
-#pragma unroll
-        for (int p = L - 1; p >= 0; --p) {
-            s0 = max(s0, (uint32_t)ru[b][p][lane]);
-            s1 = max(s1, (uint32_t)td[p][lane]);
-            const int t = (int)tc[b][p][lane];
-            const uint32_t b0 = s0 * 0x01010101u, b1 = s1 * 0x01010101u;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const int kb = min(max(t - 1 - 4 * w, 0), 4);
-                const uint32_t m = (uint32_t)(0xffffffffull << (8 * kb));
-                w0[w] = (b0 & m) | (w0[w] & ~m);
-                w1[w] = (b1 & m) | (w1[w] & ~m);
-            }
-        }
+        uint32_t w0[REL_NW], w1[REL_NW];
+        relation_maxima<L>([&](int p) { return (uint32_t)tc[b][p][lane]; },
+                           [&](int p) { return (uint32_t)ru[b][p][lane]; },
+                           [&](int p) { return (uint32_t)td[p][lane]; }, w0, w1);
         if (bad) {
 #pragma unroll
-            for (int w = 0; w < NW; ++w) w0[w] = w1[w] = 0xffffffffu;
+            for (int w = 0; w < REL_NW; ++w) w0[w] = w1[w] = 0xffffffffu;
             if (b == 0 && lane < rows_here) atomicAdd(n_bad, 1ull);
         }
         // rows are dword aligned (REL_RS = 196 bytes) and so is each 32-byte block
         uint32_t* d0 = reinterpret_cast<uint32_t*>(rows + lane * REL_RS + (0 * 3 + b) * REL_T);
         uint32_t* d1 = reinterpret_cast<uint32_t*>(rows + lane * REL_RS + (1 * 3 + b) * REL_T);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
+        for (int w = 0; w < REL_NW; ++w) {
             d0[w] = w0[w];
             d1[w] = w1[w];
         }

@@ -521,6 +521,10 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t s_kv[2][CPW][MAX_KNOBS];   // current, pending knobs
     __shared__ uint32_t s_sel[CPW];
     __shared__ uint32_t s_any;
+    // both outcomes' rows as the tree kernel reads them: tile words of the
+    // loop-context features and, in Eq. 4 runs, of the relation features
+    __shared__ uint32_t s_tile[2][CPW][Q | 1];
+    __shared__ uint32_t s_rel[2][CPW][REL_Q | 1];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int64_t c0 = (int64_t)blockIdx.x * CPW;
@@ -565,20 +569,55 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     int64_t thr_i = a.fin == FIN_STEP ? c * a.steps + a.fin_step : c;
     asm volatile("" : "+v"(thr_i));   // one load from either table (not two loads and a join)
     const float thr_v = thr_b[thr_i];
-    // tile-layout words of the packed rows this thread writes at the end
-    // (quads (tid + m * CHAIN_WG) / 16, clamped to the last so that every
-    // lane loads)
-    constexpr int PACK_ITERS = (CPW * Q + CHAIN_WG - 1) / CHAIN_WG;
-    uint32_t src4[PACK_ITERS];
+    // features at the tile positions of quad `lane` (the last quad's for the
+    // lanes past it, so that every lane loads)
+    const uint32_t src4 =
+        a.fident ? 0u : *reinterpret_cast<const uint32_t*>(a.fsrc + 4 * (lane < a.fq ? lane : a.fq - 1));
+
+    // Rows first, first + stride, ... (count of them; row 2j + o is chain j's
+    // candidate after outcome o) from their features to tile words, by one
+    // wave.  Compact tiles: lane q packs quad q (4x+3 per byte, padding 0; a
+    // feature value x <= 63 makes (x << 2) | 3 stay within its byte); tiles of
+    // every feature in order are read from the rows themselves.  Eq. 4 runs:
+    // lanes take (row, buffer) pairs for the context relation features
+    // (Section 4), laid out [pair][buffer][t - 1].  Made here, beside the
+    // fold, rather than after the decision: Eq. 4's chain kernel went from
+    // 21.0 to 16.2 us (12 x 512 chains, 1000 + 1000 trees).
+    auto finish_rows = [&](int first, int stride, int count) {
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // this wave's own rows are in LDS
+        __builtin_amdgcn_wave_barrier();
+        if (!a.fident) {
+#pragma unroll 4
+            for (int i = 0; i < count; ++i) {
+                const int jo = first + i * stride, j = jo >> 1, o = jo & 1;
+                const uint8_t* row = frow[o][j];
+                uint32_t w = 0u;
 #pragma unroll
-    for (int m = 0; m < PACK_ITERS; ++m) src4[m] = 0u;
-    if (!a.fident) {
-#pragma unroll
-        for (int m = 0; m < PACK_ITERS; ++m) {
-            const int q = (tid + m * CHAIN_WG) >> 4;
-            src4[m] = *reinterpret_cast<const uint32_t*>(a.fsrc + 4 * (q < a.fq ? q : a.fq - 1));
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const uint32_t f = (src4 >> (8 * i4)) & 0xffu;
+                    const uint32_t x = row[f < (uint32_t)N::F ? f : 0u];
+                    if (f != 0xffu) w |= ((x << 2) | 3u) << (8 * i4);
+                }
+                if (lane < a.fq) s_tile[o][j][lane] = w;
+            }
         }
-    }
+        if (a.Fr) {
+            for (int i = lane; i < 3 * count; i += 64) {
+                const int jo = first + (i / 3) * stride, b = i % 3, j = jo >> 1, o = jo & 1;
+                const uint8_t* row = frow[o][j];
+                const uint8_t* tdr = tdrow[o][j];
+                uint32_t w0[REL_NW], w1[REL_NW];
+                relation_maxima<L>([&](int p) { return (uint32_t)row[p * 11 + 2 + 3 * b]; },
+                                   [&](int p) { return (uint32_t)row[p * 11 + 3 + 3 * b]; },
+                                   [&](int p) { return (uint32_t)tdr[p]; }, w0, w1);
+#pragma unroll
+                for (int w = 0; w < REL_NW; ++w) {
+                    s_rel[o][j][b * REL_NW + w] = (w0[w] << 2) | 0x03030303u;
+                    s_rel[o][j][(3 + b) * REL_NW + w] = (w1[w] << 2) | 0x03030303u;
+                }
+            }
+        }
+    };
 
     if (a.fin == FIN_NONE) {
         // No pending candidate: the first draw of fresh chains, or a move
@@ -606,11 +645,16 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
             s_sel[tid] = 0u;
         }
         lds_barrier();
-        // lane gr of group gj: loop gr of chain gj's candidate
+        // lane gr of group gj: loop gr of chain gj's candidate (a wave makes
+        // four chains' rows and finishes them)
         if (gvalid && gr < L) {
             uint32_t nx[MAX_KNOBS];
             unpack_pairs(rec[gj].nx[0], nx);
             row_features<TMPL>(desc_of(gj), facp, nx, gr, a.Fr != nullptr, frow[0][gj], tdrow[0][gj]);
+        }
+        {
+            const int left = nc - 4 * wave;
+            finish_rows(8 * wave, 2, left < 0 ? 0 : (left < 4 ? left : 4));
         }
         lds_barrier();
     } else {
@@ -676,9 +720,10 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
                     if (j < sd.n_knobs) cfg += (uint64_t)s_kv[1][t0][j] * sd.radix[j];
                 rec[t0].cfg = cfg;
             }
-            // both next candidates of every chain and their loop features:
-            // task t is loop t % L of outcome (t / L) & 1 of chain t / (2L)
-            // (an initial candidate is always accepted: no reject outcome)
+            // both next candidates of every chain, their loop features and
+            // their finished rows: wave w takes rows w - 1, w + 2, ..., row
+            // 2j + o being chain j's candidate after outcome o (an initial
+            // candidate is always accepted: its reject rows are not read)
             if (a.draw == DRAW_PROPOSE) {
                 // the moves first, lane i < 2 nc of every building wave making
                 // the move of chain i / 2 from state i & 1 into the wave's own
@@ -701,13 +746,16 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
                 }
                 __builtin_amdgcn_s_waitcnt(0xc07f);
                 __builtin_amdgcn_wave_barrier();
-                for (int t = t0; t < nc * 2 * L; t += CHAIN_WG - 64) {
-                    const int l = t % L, jo = t / L, j = jo >> 1, o = jo & 1;
+                constexpr int BW = CHAIN_WG / 64 - 1;
+                const int mine = (2 * nc - (wave - 1) + BW - 1) / BW;
+                for (int t = lane; t < mine * L; t += 64) {
+                    const int l = t % L, jo = wave - 1 + BW * (t / L), j = jo >> 1, o = jo & 1;
                     if (o == 1 && a.fin == FIN_INIT) continue;
                     uint32_t nx[MAX_KNOBS];
                     unpack_pairs(mv[jo], nx);
                     row_features<TMPL>(desc_of(j), facp, nx, l, a.Fr != nullptr, frow[o][j], tdrow[o][j]);
                 }
+                finish_rows(wave - 1, BW, mine);
             }
         }
         // score known (wave 0), candidates built (waves 1-3)
@@ -786,60 +834,25 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     }
 
     // the rows of each chain's next candidate: outcome s_sel[j] (rows and
-    // choices are in LDS since the last barrier)
+    // choices are in LDS since the last barrier), consecutive lanes on
+    // consecutive chains
     if (a.Fr) {
-        // context relation features of the candidate (Section 4): output
-        // o = [pair][buffer b][t - 1] is the largest value over the loops
-        // whose touch count of b is below 2^t (bitlen(touch) <= t), the value
-        // being bitlen(reuse ratio of b) for pair 0, bitlen(top-down) for
-        // pair 1; 0 when no loop qualifies.  Lane gr of group gj makes
-        // outputs gr, gr + 16, ...
-        __shared__ __attribute__((aligned(16))) uint8_t rrow[CPW][REL_F];
-        if (gvalid) {
-            const uint8_t* fr = frow[s_sel[gj]][gj];
-            const uint8_t* tr = tdrow[s_sel[gj]][gj];
-#pragma unroll 1
-            for (int o = gr; o < REL_F; o += 16) {
-                const int pair = o / 96, b = (o >> 5) % 3;
-                const uint32_t t = (uint32_t)(o & 31) + 1u;
-                uint32_t v = 0u;
-#pragma unroll
-                for (int l = 0; l < L; ++l) {
-                    const uint32_t bt = fr[l * 11 + 2 + 3 * b];
-                    const uint32_t x = pair ? (uint32_t)tr[l] : (uint32_t)fr[l * 11 + 3 + 3 * b];
-                    v = (bt <= t && x > v) ? x : v;
-                }
-                rrow[gj][o] = (uint8_t)v;
-            }
-        }
-        lds_barrier();
         for (int idx = tid; idx < CPW * REL_Q; idx += CHAIN_WG) {
             const int q = idx >> 4, j = idx & (CPW - 1);
-            if (j >= nc) continue;
-            const uint32_t w = (*reinterpret_cast<const uint32_t*>(&rrow[j][4 * q]) << 2) | 0x03030303u;
-            a.Fr[(int64_t)q * a.fg_stride + c0 + j] = w;
+            if (j < nc) a.Fr[(int64_t)q * a.fg_stride + c0 + j] = s_rel[s_sel[j]][j][q];
         }
     }
-    // packed rows out in the tree kernel's tile layout (4x+3 per byte,
-    // padding 0), consecutive lanes on consecutive chains
-    // (a feature value x <= 63 makes (x << 2) | 3 stay within its byte)
-#pragma unroll
-    for (int m = 0; m < PACK_ITERS; ++m) {
-        const int idx = tid + m * CHAIN_WG;
+    for (int idx = tid; idx < CPW * a.fq; idx += CHAIN_WG) {
         const int q = idx >> 4, j = idx & (CPW - 1);
-        if (q >= a.fq || j >= nc) continue;
-        const uint8_t* row = frow[s_sel[j]][j];
-        uint32_t w = 0u;
+        if (j >= nc) continue;
+        const uint32_t o = s_sel[j];
+        uint32_t w;
         if (a.fident) {
             constexpr uint32_t LAST = (N::F & 3) ? (1u << (8 * (N::F & 3))) - 1u : 0xffffffffu;
-            w = (*reinterpret_cast<const uint32_t*>(row + 4 * q) << 2) | 0x03030303u;
+            w = (*reinterpret_cast<const uint32_t*>(frow[o][j] + 4 * q) << 2) | 0x03030303u;
             if (q == Q - 1) w &= LAST;
         } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t f = (src4[m] >> (8 * i)) & 0xffu;
-                if (f != 0xffu) w |= (((uint32_t)row[f] << 2) | 3u) << (8 * i);
-            }
+            w = s_tile[o][j][q];
         }
         a.Fg[(int64_t)q * a.fg_stride + c0 + j] = w;
     }
