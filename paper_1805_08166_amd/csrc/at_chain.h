@@ -297,5 +297,44 @@ __device__ __forceinline__ float fold_row(float s, const float* __restrict__ row
     return s;
 }
 
+// The knob a step changes and the value it draws among the knob's other
+// values, before the shift past the current value (block (chain, step, 0, 0)).
+// Neither depends on the chain's state, so they are drawn ahead of time.
+__device__ __forceinline__ void draw_move(const SpaceDesc& sd, uint32_t k0, uint32_t k1, uint32_t chain,
+                                          uint32_t step, int& jm, uint32_t& v, uint64_t& radix) {
+    const U4 rr = philox(k0, k1, U4{chain, step, 0u, 0u});
+    jm = -1;
+    v = 0u;
+    radix = 0;
+    if (sd.n_mut > 0) {
+        jm = sd.mut[uniform_below(rr.x, (uint32_t)sd.n_mut)];
+        v = uniform_below(rr.y, sd.knob_size[jm] - 1u);
+        radix = sd.radix[jm];
+    }
+}
+
+// base with knob jm moved to the drawn value v shifted past base's value
+// (jm < 0: no knob can move), and the configuration index of the result.
+__device__ __forceinline__ void apply_move(const uint32_t (&base)[MAX_KNOBS], uint64_t base_cfg, int jm, uint32_t v,
+                                           uint64_t radix, uint32_t (&out)[MAX_KNOBS], uint64_t& cfg) {
+    uint32_t old = 0;
+#pragma unroll
+    for (int j = 0; j < MAX_KNOBS; ++j) {
+        old = (j == jm) ? base[j] : old;
+        out[j] = (j == jm) ? v + (v >= base[j] ? 1u : 0u) : base[j];
+    }
+    // the index moves by (new - old) times the knob's weight
+    const uint32_t nv = v + (v >= old ? 1u : 0u);
+    cfg = jm < 0 ? base_cfg
+                 : (nv >= old ? base_cfg + (uint64_t)(nv - old) * radix : base_cfg - (uint64_t)(old - nv) * radix);
+}
+
+// Words between trees of the local forms (local_tree_stride): whole trees,
+// or tops only (tail).
+__host__ __device__ constexpr int local_stride(int depth, bool tail) {
+    const int w = tail ? (depth >= 2 ? 1 << (depth - 2) : 1) : 3 << (depth - 1);
+    return w + ((1 - w) % 32 + 32) % 32;
+}
+
 }  // namespace dev
 }  // namespace at

@@ -312,6 +312,7 @@ struct LocalPlan {
     int n_chunks = 0;         // chunks walked per step
     int resident = 0;         // 1: every tree stays in LDS, loaded once
     int tail = 0;             // 1: tree tops resident in LDS, last level and leaves gathered
+    int single = 0;           // 1: the single-pass kernel (at_sa_single.hip)
     uint32_t ring_bytes = 0;
     int walk_waves = 0;       // waves 1 .. walk_waves walk, later ones load
     uint32_t off_ring = 0, off_lv = 0, off_lists = 0, off_rec = 0, off_frow = 0, off_any = 0, off_desc = 0;
@@ -325,6 +326,11 @@ bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& 
 hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chains_s& ch, const LocalPlan& pl,
                            int steps, bool init, const float* thr, at_entry* best, at_entry* trace,
                            hipStream_t stream);
+// The single-pass kernel: pl.cpb set; true when it fits (pl is then filled).
+bool plan_single(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& ch, LocalPlan& pl);
+hipError_t launch_sa_single(const at_space_s& sp, const EnsembleDesc& e, at_chains_s& ch, const LocalPlan& pl,
+                            int steps, bool init, const float* thr, at_entry* best, at_entry* trace,
+                            hipStream_t stream);
 // Start and stop events for the next launch of one kind (0: the walk
 // kernel, 1: the chain kernel), or nulls when the chains are not profiled.
 hipError_t next_events(at_chains_s& ch, int kind, hipEvent_t& start, hipEvent_t& stop);

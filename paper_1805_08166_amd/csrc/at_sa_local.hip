@@ -91,38 +91,6 @@ __device__ __forceinline__ void load_trees(const LocalArgs& a, uint8_t* dst, int
 }
 
 
-// The knob a step changes and the value it draws among the knob's other
-// values, before the shift past the current value (block (chain, step, 0, 0)).
-// Neither depends on the chain's state, so they are drawn ahead of time.
-__device__ __forceinline__ void draw_move(const SpaceDesc& sd, uint32_t k0, uint32_t k1, uint32_t chain,
-                                          uint32_t step, int& jm, uint32_t& v, uint64_t& radix) {
-    const U4 rr = philox(k0, k1, U4{chain, step, 0u, 0u});
-    jm = -1;
-    v = 0u;
-    radix = 0;
-    if (sd.n_mut > 0) {
-        jm = sd.mut[uniform_below(rr.x, (uint32_t)sd.n_mut)];
-        v = uniform_below(rr.y, sd.knob_size[jm] - 1u);
-        radix = sd.radix[jm];
-    }
-}
-
-// base with knob jm moved to the drawn value v shifted past base's value
-// (jm < 0: no knob can move), and the configuration index of the result.
-__device__ __forceinline__ void apply_move(const uint32_t (&base)[MAX_KNOBS], uint64_t base_cfg, int jm, uint32_t v,
-                                           uint64_t radix, uint32_t (&out)[MAX_KNOBS], uint64_t& cfg) {
-    uint32_t old = 0;
-#pragma unroll
-    for (int j = 0; j < MAX_KNOBS; ++j) {
-        old = (j == jm) ? base[j] : old;
-        out[j] = (j == jm) ? v + (v >= base[j] ? 1u : 0u) : base[j];
-    }
-    // the index moves by (new - old) times the knob's weight
-    const uint32_t nv = v + (v >= old ? 1u : 0u);
-    cfg = jm < 0 ? base_cfg
-                 : (nv >= old ? base_cfg + (uint64_t)(nv - old) * radix : base_cfg - (uint64_t)(old - nv) * radix);
-}
-
 // FAST instances run the single-pass plans with at most four chains per
 // workgroup and full workgroups (the launcher picks them); the others run
 // every other plan.  Compiling the two apart keeps each one's uniform state
@@ -823,6 +791,9 @@ bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& 
     auto lv_bytes = [&](int ct) { return al16((size_t)cpb * (2 * (size_t)ct + 4) * 4); };
     pl = LocalPlan{};
     pl.cpb = cpb;
+    if (plan_single(sp, e, ch, pl)) return true;
+    pl = LocalPlan{};
+    pl.cpb = cpb;
     pl.threads = threads;
     pl.grid = (int)((n + cpb - 1) / cpb);
     pl.off_ring = (uint32_t)tile;
@@ -904,8 +875,6 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
                            hipStream_t stream) {
     const int64_t n = ch.n_chains;
     if (n == 0) return hipSuccess;
-    // the kernel's tile fill and its wave roles assume full workgroups
-    if (pl.threads != LOCAL_WG_MAX) return hipErrorInvalidConfiguration;
     hipError_t err;
     if (!ch.d_meta.p) {
         err = hipMalloc(&ch.d_meta.p, (size_t)n * sizeof(ChainMeta));
@@ -915,6 +884,16 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
         }
         ch.d_meta.bytes = (size_t)n * sizeof(ChainMeta);
     }
+    if (pl.single) {
+        ch.events_used[0] = ch.events_used[1] = 0;
+        hipEvent_t start = nullptr, stop = nullptr;
+        if ((err = next_events(ch, 0, start, stop)) != hipSuccess) return err;
+        if (start && (err = hipEventRecord(start, stream)) != hipSuccess) return err;
+        if ((err = launch_sa_single(sp, e, ch, pl, steps, init, thr, best, trace, stream)) != hipSuccess) return err;
+        return stop ? hipEventRecord(stop, stream) : hipSuccess;
+    }
+    // the kernel's tile fill and its wave roles assume full workgroups
+    if (pl.threads != LOCAL_WG_MAX) return hipErrorInvalidConfiguration;
     LocalArgs a{};
     a.descs = static_cast<const SpaceDesc*>(sp.d_descs.p);
     a.offsets = static_cast<const int64_t*>(sp.d_offsets.p);

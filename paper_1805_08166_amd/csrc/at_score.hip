@@ -54,23 +54,17 @@ struct RowsArgs {
     int T;
     int ct;                   // trees per chunk, a multiple of 4
     int n_chunks;
-    const uint32_t* tw;       // local form, a tree every rows_stride words
+    const uint32_t* tw;       // local form, a tree every local_stride words
     const uint4* tail;
     uint32_t off_ring, ring_bytes;
     uint32_t off_lv;
     int lv_stride;            // floats per row of leaf values
 };
 
-// Words between trees in the ring (local_tree_stride of the form).
-__host__ __device__ constexpr int rows_stride(int depth, bool tail) {
-    const int w = tail ? (depth >= 2 ? 1 << (depth - 2) : 1) : 3 << (depth - 1);
-    return w + ((1 - w) % 32 + 32) % 32;
-}
-
 template <int DEPTH, bool TAIL>
 __global__ __launch_bounds__(1024) void k_rows(RowsArgs a) {
     constexpr int WALK = TAIL ? DEPTH - 1 : DEPTH;
-    constexpr uint32_t TB = (uint32_t)rows_stride(DEPTH, TAIL) * 4u;
+    constexpr uint32_t TB = (uint32_t)local_stride(DEPTH, TAIL) * 4u;
     constexpr uint32_t NBB = 4u << (DEPTH - 1);   // node block bytes of a whole tree
     extern __shared__ uint4 lds4[];
     uint8_t* lds = reinterpret_cast<uint8_t*>(lds4);
@@ -399,7 +393,7 @@ struct RowsPlan {
 
 // LDS layout of a plan; false when it takes more than `limit` bytes.
 bool rows_layout(const EnsembleDesc& e, RowsPlan& pl, RowsArgs& a, size_t limit) {
-    const uint32_t tb = (uint32_t)rows_stride(e.depth, pl.tail) * 4u;
+    const uint32_t tb = (uint32_t)local_stride(e.depth, pl.tail) * 4u;
     a.quads = (e.n_features + 3) / 4;
     a.tw = pl.tail ? e.local_top : e.local_full;
     a.R = pl.R;
