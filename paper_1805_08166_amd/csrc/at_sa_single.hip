@@ -24,7 +24,7 @@
 // the rows into a 64-column tile each round and kept the chains' books in
 // wave 0, took 3.76 us a step on the C2 search (1024 chains, 500 trees of
 // depth 8) and 2.50 on the GEMM one (64 chains, 100 trees of depth 6); this
-// one MEASURED.
+// one 3.3 and 1.26.
 #include <type_traits>
 
 #include "at_chain.h"
@@ -87,7 +87,8 @@ struct SingleArgs {
     // dynamic LDS layout (byte offsets; the trees are at 0)
     uint32_t off_lv, off_lists, off_rec, off_frow, off_desc;
     int lv_stride;            // floats per chain row of leaf values
-    uint32_t frow_stride;     // bytes between the row sets of the two outcomes
+    uint32_t frow_stride;     // bytes between row sets: set 2 (r & 1) + o is round r's candidates after outcome o
+    int early;                // the evaluating waves do not walk (see k_single)
 };
 
 // One level of a tree whose row's features are read from LDS byte rb + f:
@@ -197,8 +198,8 @@ __device__ __forceinline__ void walk_row(const uint32_t (&nb)[G], uint32_t rb, u
     for (int g = 0; g < G; ++g) q[g] = 2u * p[g] + (x[g] >= (node[g] & 0xffu) ? 1u : 0u) - (1u << DEPTH);
 }
 
-template <int TMPL, int DEPTH, bool TAIL>
-__global__ __launch_bounds__(1024) void k_single(SingleArgs a) {
+template <int TMPL, int DEPTH, bool TAIL, int NT>
+__global__ __launch_bounds__(NT) void k_single(SingleArgs a) {
     using N = Nest<TMPL>;
     constexpr int RS = (N::F + 3) / 4 * 4 + 4;            // feature row stride: an odd number of dwords
     static_assert(RS / 4 % 2 == 1, "rows spread over the LDS banks");
@@ -216,7 +217,10 @@ __global__ __launch_bounds__(1024) void k_single(SingleArgs a) {
     uint64_t* s_fac = reinterpret_cast<uint64_t*>(lds + a.off_desc + sizeof(SpaceDesc));
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int nthreads = (int)blockDim.x, nwaves = nthreads >> 6;
+    constexpr int nthreads = NT, nwaves = nthreads >> 6;
+    // (with 1024 threads every lane walks, and two copies of the evaluation
+    // would not fit the registers)
+    const bool early = NT == 512 && a.early;
     const int cpb = a.cpb;
     const int64_t c0 = (int64_t)blockIdx.x * cpb;
     const int nc = (a.n - c0 < cpb) ? (int)(a.n - c0) : cpb;
@@ -378,53 +382,130 @@ __global__ __launch_bounds__(1024) void k_single(SingleArgs a) {
         group_offer(lists + (on ? g : 0) * k, R, k, gl, 0xffffull << (16 * g), q);
     };
 
-    const int S = nthreads / cpb, ja = tid & (cpb - 1), slot = tid / cpb;
+    // Everything beside the fold depends on the round's candidate and on
+    // earlier rounds alone, so a wave that does not walk does its share
+    // during the walk: the evaluating waves when the others take all trees in
+    // as few passes without them (`early`: small ensembles, whose fold is
+    // shorter than an evaluation), and any helper wave past the last tree.
+    const int ew = early ? (cpb + 1) / 2 : 0;   // evaluating waves kept from walking
+    const bool walks = wave == 0 || wave > ew;
+    const int wt = tid - (wave == 0 ? 0 : 64 * ew);
+    const int S = (nthreads - 64 * ew) / cpb, ja = wt & (cpb - 1), slot = wt / cpb;
     const int jr = ja < nc ? ja : nc - 1;
     const int per = (a.T + S - 1) / S;            // trees a lane
-    // phase A for G trees a pass from tree `base` on
-    auto walk_pass = [&](auto gc, int base, uint32_t rb) {
-        constexpr int G = decltype(gc)::value;
-        uint32_t nb[G], q[G], v[G];
-        int ti[G];
+    const bool idle = walks && wave > 0 && (wt & ~63) / cpb >= a.T;   // no tree for any lane of the wave
+    // phase A for trees base + slot, + S, ...: H times G of them, G walked
+    // together.  With tails the first half's records are on their way while
+    // the second half is walked (C2 search: 3.42 us a step against 3.65 with
+    // both walked first).
+    auto walk_pass = [&](auto gc, auto hc, int base, uint32_t rb) {
+        constexpr int G = decltype(gc)::value, H = decltype(hc)::value;
+        uint4 rec4[TAIL ? G * H : 1];
+        int ti[G * H];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int t = base + slot + g * S;
-            ti[g] = t < a.T ? t : -1;
-            nb[g] = lbase + (uint32_t)(t < a.T ? t : 0) * TB;
-        }
-        walk_row<(WALK > 0 ? WALK : 1), G>(nb, rb, q);
-        if constexpr (TAIL) {
-            uint4 rec4[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) rec4[g] = a.tail_rec[((size_t)(ti[g] >= 0 ? ti[g] : 0) << WALK) + q[g]];
+        for (int h = 0; h < H; ++h) {
+            uint32_t nb[G], q[G];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const uint32_t x4 = lds[rb - lbase + row_byte(rec4[g].x)];
-                v[g] = x4 >= (rec4[g].x & 0xffu) ? rec4[g].z : rec4[g].y;
+                const int t = base + slot + (h * G + g) * S;
+                ti[h * G + g] = t < a.T ? t : -1;
+                nb[g] = lbase + (uint32_t)(t < a.T ? t : 0) * TB;
             }
-        } else {
+            walk_row<(WALK > 0 ? WALK : 1), G>(nb, rb, q);
 #pragma unroll
-            for (int g = 0; g < G; ++g) v[g] = *reinterpret_cast<const uint32_t*>(lds + (nb[g] - lbase) + NBB + 4u * q[g]);
+            for (int g = 0; g < G; ++g) {
+                const int t = ti[h * G + g];
+                if constexpr (TAIL) {
+                    rec4[h * G + g] = a.tail_rec[((size_t)(t >= 0 ? t : 0) << WALK) + q[g]];
+                } else {
+                    const uint32_t v = *reinterpret_cast<const uint32_t*>(lds + (nb[g] - lbase) + NBB + 4u * q[g]);
+                    if (t >= 0 && ja < nc) lv[ja * a.lv_stride + t] = __uint_as_float(v);
+                }
+            }
         }
+        if constexpr (TAIL) {
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-            if (ti[g] >= 0 && ja < nc) lv[ja * a.lv_stride + ti[g]] = __uint_as_float(v[g]);
+            for (int i = 0; i < G * H; ++i) {
+                const uint32_t x4 = lds[rb - lbase + row_byte(rec4[i].x)];
+                const uint32_t v = x4 >= (rec4[i].x & 0xffu) ? rec4[i].z : rec4[i].y;
+                if (ti[i] >= 0 && ja < nc) lv[ja * a.lv_stride + ti[i]] = __uint_as_float(v);
+            }
+        }
     };
     using One = std::integral_constant<int, 1>;
-    using Two = std::integral_constant<int, 2>;
-    using Four = std::integral_constant<int, 4>;
+    using Each = std::integral_constant<int, TAIL ? 1 : 2>;    // two trees a pass
+    using Pair = std::integral_constant<int, TAIL ? 2 : 4>;    // four trees a pass
+    using Halves = std::integral_constant<int, TAIL ? 2 : 1>;
+
+    // Both candidates that can follow round r, with the features of both
+    // (waves 1 .. ceil(cpb / 2)): item (v * cpb + j) * 16 + l is loop l of
+    // chain j's next candidate after outcome v of this round.  A wave that
+    // does this during the walk passes the barrier after the walk halfway.
+    auto make_next = [&](int r, bool halfway) {
+        const int it = tid - 64;
+        const int l = it & 15, jv = it >> 4, j = jv & (cpb - 1), v = jv >= cpb ? 1 : 0;
+        const bool on = it < 32 * cpb && j < nc && l < N::L;
+        uint32_t nx[MAX_KNOBS];
+        if (on) {
+            SingleRec& R = rec[j];
+            const uint32_t o = R.ssel[r & 3], op = R.ssel[(r + 3) & 3];
+            // this round's candidate (v = 0; after the initial draw, which is
+            // always accepted, also v = 1), or the configuration the round
+            // starts from: the previous round's candidate if it was accepted,
+            // else what that round started from
+            const bool from_cand = v == 0 || (a.init && r == 0);
+            const uint32_t* src = from_cand ? R.snx[r & 3][o]
+                                : o == 0u   ? R.snx[(r + 3) & 3][op]
+                                            : R.curk[(r + 1) & 1];
+            const uint64_t bcfg = from_cand ? R.scfg[r & 3][o]
+                                : o == 0u   ? R.scfg[(r + 3) & 3][op]
+                                            : R.curcfg[(r + 1) & 1];
+            uint32_t w[MAX_KNOBS / 2], base[MAX_KNOBS];
+#pragma unroll
+            for (int i = 0; i < MAX_KNOBS / 2; ++i) w[i] = src[i];
+            if (v == 1 && l == 0) {
+#pragma unroll
+                for (int i = 0; i < MAX_KNOBS / 2; ++i) R.curk[r & 1][i] = w[i];
+                R.curcfg[r & 1] = bcfg;
+            }
+            uint64_t ncfg;
+            unpack(w, base);
+            const int sl = (r + 1) & 1;
+            apply_move(base, bcfg, R.mvj[sl], R.mvv[sl], R.mvr[sl], nx, ncfg);
+            if (l == 0 && r + 1 < rounds) {
+                pack(nx, R.snx[(r + 1) & 3][v]);
+                R.scfg[(r + 1) & 3][v] = ncfg;
+            }
+        }
+        if (halfway) lds_barrier();
+        if (on && r + 1 < rounds) eval_loop(nx, j, l, frow + (2 * ((r + 1) & 1) + v) * a.frow_stride + j * RS);
+    };
+    // The other work beside a fold: waves 3 and 4 and the last one.
+    auto side_work = [&](int r) {
+        if (wave == 3 && r > 0) offer_round(r - 1);
+        if (wave == 4 && lane < nc && r + 2 < rounds) draw_into(lane, r + 2);
+        if (wave == nwaves - 1 && lane < nc && r + 1 < rounds)
+            rec[lane].thr[(r + 1) & 1] = a.thr[(c0 + lane) * a.steps + first_step + r + 1];
+    };
 
     for (int r = 0; r < rounds; ++r) {
         // ---- A: walk
-        {
+        if (NT == 512 && !walks) {
+            make_next(r, true);      // with this round's barrier after the walk
+            lds_barrier();
+            continue;
+        }
+        if (idle) {
+            side_work(r);
+        } else {
             const uint32_t o = rec[jr].ssel[r & 3];
-            const uint32_t rb = lbase + a.off_frow + o * a.frow_stride + (uint32_t)jr * RS;
+            const uint32_t rb = lbase + a.off_frow + (2u * (uint32_t)(r & 1) + o) * a.frow_stride + (uint32_t)jr * RS;
             if (per == 1) {
-                if (slot < a.T) walk_pass(One{}, 0, rb);
+                if (slot < a.T) walk_pass(One{}, One{}, 0, rb);
             } else if (per == 2) {
-                walk_pass(Two{}, 0, rb);
+                walk_pass(Each{}, Halves{}, 0, rb);
             } else {
-                for (int base = 0; base < a.T; base += 4 * S) walk_pass(Four{}, base, rb);
+                for (int base = 0; base < a.T; base += 4 * S) walk_pass(Pair{}, Halves{}, base, rb);
             }
         }
         lds_barrier();
@@ -444,52 +525,8 @@ __global__ __launch_bounds__(1024) void k_single(SingleArgs a) {
                 if (acc) cur_s = sc;
             }
         } else {
-            // item (v * cpb + j) * 16 + l: loop l of chain j's next candidate
-            // after outcome v of this round
-            const int it = tid - 64;
-            if (it < 32 * cpb) {
-                const int l = it & 15, jv = it >> 4, j = jv & (cpb - 1), v = jv >= cpb ? 1 : 0;
-                if (j < nc && l < N::L) {
-                    SingleRec& R = rec[j];
-                    const uint32_t o = R.ssel[r & 3], op = R.ssel[(r + 3) & 3];
-                    // this round's candidate (v = 0; after the initial draw,
-                    // which is always accepted, also v = 1), or the
-                    // configuration the round starts from: the previous
-                    // round's candidate if it was accepted, else what that
-                    // round started from
-                    const bool from_cand = v == 0 || (a.init && r == 0);
-                    const uint32_t* src = from_cand ? R.snx[r & 3][o]
-                                        : o == 0u   ? R.snx[(r + 3) & 3][op]
-                                                    : R.curk[(r + 1) & 1];
-                    const uint64_t bcfg = from_cand ? R.scfg[r & 3][o]
-                                        : o == 0u   ? R.scfg[(r + 3) & 3][op]
-                                                    : R.curcfg[(r + 1) & 1];
-                    uint32_t w[MAX_KNOBS / 2];
-#pragma unroll
-                    for (int i = 0; i < MAX_KNOBS / 2; ++i) w[i] = src[i];
-                    if (v == 1 && l == 0) {
-#pragma unroll
-                        for (int i = 0; i < MAX_KNOBS / 2; ++i) R.curk[r & 1][i] = w[i];
-                        R.curcfg[r & 1] = bcfg;
-                    }
-                    if (r + 1 < rounds) {
-                        uint32_t base[MAX_KNOBS], nx[MAX_KNOBS];
-                        uint64_t ncfg;
-                        unpack(w, base);
-                        const int sl = (r + 1) & 1;
-                        apply_move(base, bcfg, R.mvj[sl], R.mvv[sl], R.mvr[sl], nx, ncfg);
-                        if (l == 0) {
-                            pack(nx, R.snx[(r + 1) & 3][v]);
-                            R.scfg[(r + 1) & 3][v] = ncfg;
-                        }
-                        eval_loop(nx, j, l, frow + v * a.frow_stride + j * RS);
-                    }
-                }
-            }
-            if (wave == 3 && r > 0) offer_round(r - 1);
-            if (wave == 4 && lane < nc && r + 2 < rounds) draw_into(lane, r + 2);
-            if (wave == nwaves - 1 && lane < nc && r + 1 < rounds)
-                rec[lane].thr[(r + 1) & 1] = a.thr[(c0 + lane) * a.steps + first_step + r + 1];
+            if (!early && wave <= (cpb + 1) / 2) make_next(r, false);
+            if (!idle) side_work(r);
         }
         lds_barrier();
     }
@@ -517,17 +554,23 @@ __global__ __launch_bounds__(1024) void k_single(SingleArgs a) {
     }
 }
 
-template <int TMPL, int DEPTH, bool TAIL>
-hipError_t launch_single_t(const SingleArgs& a, const LocalPlan& pl, hipStream_t stream) {
+template <int TMPL, int DEPTH, bool TAIL, int NT>
+hipError_t launch_single_nt(const SingleArgs& a, const LocalPlan& pl, hipStream_t stream) {
     static bool configured = false;
-    const void* fn = reinterpret_cast<const void*>(&k_single<TMPL, DEPTH, TAIL>);
+    const void* fn = reinterpret_cast<const void*>(&k_single<TMPL, DEPTH, TAIL, NT>);
     if (!configured) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SINGLE_LDS_BYTES);
         if (e != hipSuccess) return e;
         configured = true;
     }
     void* args[] = {const_cast<SingleArgs*>(&a)};
-    return hipLaunchKernel(fn, dim3(pl.grid), dim3(pl.threads), args, pl.lds_bytes, stream);
+    return hipLaunchKernel(fn, dim3(pl.grid), dim3(NT), args, pl.lds_bytes, stream);
+}
+
+template <int TMPL, int DEPTH, bool TAIL>
+hipError_t launch_single_t(const SingleArgs& a, const LocalPlan& pl, hipStream_t stream) {
+    return pl.threads == 1024 ? launch_single_nt<TMPL, DEPTH, TAIL, 1024>(a, pl, stream)
+                              : launch_single_nt<TMPL, DEPTH, TAIL, 512>(a, pl, stream);
 }
 
 template <int TMPL, bool TAIL>
@@ -554,7 +597,8 @@ hipError_t launch_single_d(const SingleArgs& a, const LocalPlan& pl, int depth, 
 // Plan of the single-pass kernel for pl.cpb chains per workgroup (at most
 // four): whole trees when they all fit beside the chains' state, else the
 // tree tops.  False when neither does.  A lane takes one, two or four trees
-// a pass: 1024 threads when 512 would give it more than one.
+// a pass: 1024 threads when 512 would give it more than two (the C2 search,
+// 2000 tree walks a round: 1685 us a run against 1790).
 bool plan_single(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& ch, LocalPlan& pl) {
     if (pl.cpb > 4) return false;
     const int64_t n = ch.n_chains;
@@ -582,7 +626,7 @@ bool plan_single(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s&
         off += al16((size_t)pl.cpb * sizeof(SingleRec));
         pl.off_frow = (uint32_t)off;
         pl.frow_stride = (uint32_t)al16((size_t)pl.cpb * RS);
-        off += 2 * pl.frow_stride;
+        off += 4 * pl.frow_stride;
         pl.off_desc = (uint32_t)off;
         off += al16(sizeof(SpaceDesc) + (size_t)fac_max * 8);
         if (off > SINGLE_LDS_BYTES) continue;
@@ -593,7 +637,15 @@ bool plan_single(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s&
         pl.ts = ts;
         pl.ct = T;
         pl.n_chunks = 1;
-        pl.threads = T * pl.cpb > 512 ? 1024 : 512;
+        pl.threads = T * pl.cpb > 1024 ? 1024 : 512;
+        // the evaluating waves stay out of the walk when that costs no pass
+        const int ew = (pl.cpb + 1) / 2;
+        auto passes = [&](int lanes) {
+            const int S = lanes / pl.cpb, per = (T + S - 1) / S;
+            return per <= 2 ? per : (per + 3) / 4 * 4;
+        };
+        pl.walk_waves = pl.threads / 64;
+        if (pl.threads == 512 && passes(pl.threads - 64 * ew) == passes(pl.threads)) pl.walk_waves -= ew;
         pl.grid = (int)((n + pl.cpb - 1) / pl.cpb);
         pl.lds_bytes = off;
         pl.round_bytes = tail ? (double)pl.cpb * T * 64 : 0.0;
@@ -628,6 +680,7 @@ hipError_t launch_sa_single(const at_space_s& sp, const EnsembleDesc& e, at_chai
     a.tw = pl.tail ? e.local_top : e.local_full;
     a.T = e.n_trees;
     a.tail_rec = e.tail;
+    a.early = pl.walk_waves < pl.threads / 64 ? 1 : 0;
     a.off_lv = pl.off_lv;
     a.off_lists = pl.off_lists;
     a.off_rec = pl.off_rec;
