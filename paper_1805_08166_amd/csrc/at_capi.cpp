@@ -435,7 +435,7 @@ at_status at_ensemble_create(int n_trees, int depth, int n_features, const uint8
             tw[n + 1] = ((uint32_t)thr[t * n_int + n] << 16) | tile_offset(fid[t * n_int + n]);
         std::memcpy(tw + n_leaf, &leaf[t * n_leaf], n_leaf * 4);
     }
-    // compact form for the annealing kernels (layout in at_internal.h)
+    // compact form (layout in at_internal.h), which the local forms are made of
     const size_t NB = n_leaf / 2, W16 = NB + n_leaf;
     std::vector<uint32_t> words16;
     try {
@@ -472,22 +472,19 @@ at_status at_ensemble_create(int n_trees, int depth, int n_features, const uint8
         }
         std::memcpy(tw + 2 * NB, &leaf[t * n_leaf], n_leaf * 4);
     }
-    // local forms for the chain-local annealing path (layout in at_internal.h)
-    const size_t ts_full = (size_t)local_tree_stride((int)W16), ts_nodes = (size_t)local_tree_stride((int)NB);
-    std::vector<uint32_t> local_full, local_nodes;
+    // local form for the chain-local annealing path (layout in at_internal.h)
+    const size_t ts_full = (size_t)local_stride(depth, false);
+    std::vector<uint32_t> local_full;
     try {
         local_full.assign((size_t)n_trees * ts_full + 4, 0u);
-        local_nodes.assign((size_t)n_trees * ts_nodes + 4, 0u);
     } catch (...) {
         return fail(AT_E_OOM, "at_ensemble_create: host allocation");
     }
-    for (size_t t = 0; t < (size_t)n_trees; ++t) {
+    for (size_t t = 0; t < (size_t)n_trees; ++t)
         std::memcpy(local_full.data() + t * ts_full, words16.data() + t * W16, W16 * 4);
-        std::memcpy(local_nodes.data() + t * ts_nodes, words16.data() + t * W16, NB * 4);
-    }
     // split form: tops (levels 0 .. d-2) and last-level records
     const size_t top_words = depth >= 2 ? NB / 2 : 1;
-    const size_t ts_top = (size_t)local_tree_stride((int)top_words);
+    const size_t ts_top = (size_t)local_stride(depth, true);
     std::vector<uint32_t> local_top;
     std::vector<uint32_t> tail;
     try {
@@ -511,10 +508,8 @@ at_status at_ensemble_create(int n_trees, int depth, int n_features, const uint8
     if (!e) return fail(AT_E_OOM, "at_ensemble_create: host allocation");
     e->device = current_device();
     at_status st = upload(e->d_words, words.data(), words.size());
-    if (st == AT_OK) st = upload(e->d_words16, words16.data(), words16.size());
     if (st == AT_OK) st = upload(e->d_words32, words32.data(), words32.size());
     if (st == AT_OK) st = upload(e->d_local_full, local_full.data(), local_full.size());
-    if (st == AT_OK) st = upload(e->d_local_nodes, local_nodes.data(), local_nodes.size());
     if (st == AT_OK) st = upload(e->d_local_top, local_top.data(), local_top.size());
     if (st == AT_OK) st = upload(e->d_tail, tail.data(), tail.size());
     if (st != AT_OK) {
@@ -528,10 +523,8 @@ at_status at_ensemble_create(int n_trees, int depth, int n_features, const uint8
     e->desc.score6 = score6 ? 1 : 0;
     e->desc.leaf6 = leaf6 ? 1 : 0;
     e->desc.words = static_cast<const uint32_t*>(e->d_words.p);
-    e->desc.words16 = static_cast<const uint32_t*>(e->d_words16.p);
     e->desc.words32 = static_cast<const uint32_t*>(e->d_words32.p);
     e->desc.local_full = static_cast<const uint32_t*>(e->d_local_full.p);
-    e->desc.local_nodes = static_cast<const uint32_t*>(e->d_local_nodes.p);
     e->desc.local_top = static_cast<const uint32_t*>(e->d_local_top.p);
     e->desc.tail = static_cast<const uint4*>(e->d_tail.p);
     *out = e;
@@ -676,10 +669,8 @@ void at_ensemble_destroy(at_ensemble_t ens) {
     if (!ens) return;
     DeviceGuard g(ens->device);
     release(ens->d_words);
-    release(ens->d_words16);
     release(ens->d_words32);
     release(ens->d_local_full);
-    release(ens->d_local_nodes);
     release(ens->d_local_top);
     release(ens->d_tail);
     delete ens;

@@ -69,22 +69,6 @@ struct ChainRec {
     uint32_t sel;
     uint64_t cfga, cfgb;          // configuration indices of nx and nxb
     float thr;                    // the next round's Metropolis threshold
-    // drawn moves by step parity (knob, value, knob weight) and the scored
-    // candidates waiting for their offer, by round parity
-    int32_t mvj[2];
-    uint32_t mvv[2];
-    uint64_t mvr[2];
-    uint64_t pcfg[2];
-    float pscore[2];
-    // chain-local fast rounds, by round parity: the round's two candidates
-    // (outcome 0 after an accept, 1 after a reject; knobs packed in pairs,
-    // index), the outcome that holds the round's candidate, and the current
-    // configuration the round starts from
-    uint32_t snx[2][2][MAX_KNOBS / 2];
-    uint64_t scfg[2][2];
-    uint32_t ssel[2];
-    uint32_t curk[2][MAX_KNOBS / 2];
-    uint64_t curcfg[2];
 };
 
 // Offers (cfg, sc) to the best list of one chain held in LDS, with the 16
@@ -327,13 +311,6 @@ __device__ __forceinline__ void apply_move(const uint32_t (&base)[MAX_KNOBS], ui
     const uint32_t nv = v + (v >= old ? 1u : 0u);
     cfg = jm < 0 ? base_cfg
                  : (nv >= old ? base_cfg + (uint64_t)(nv - old) * radix : base_cfg - (uint64_t)(old - nv) * radix);
-}
-
-// Words between trees of the local forms (local_tree_stride): whole trees,
-// or tops only (tail).
-__host__ __device__ constexpr int local_stride(int depth, bool tail) {
-    const int w = tail ? (depth >= 2 ? 1 << (depth - 2) : 1) : 3 << (depth - 1);
-    return w + ((1 - w) % 32 + 32) % 32;
 }
 
 }  // namespace dev

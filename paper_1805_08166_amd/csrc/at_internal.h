@@ -68,9 +68,8 @@ constexpr int STAGE_CHAINS = 16;         // chains per chain-kernel workgroup
 // and 2m+1) holding (thr << 16) | tile byte offset of its feature; words
 // 2^d .. 2^(d+1)-1 hold the leaf values (float bits); word 0 is unused.
 //
-// The other paths use a second, compact form (words16) whose thresholds
-// have six bits.  Tree t occupies words16 [t*W16, (t+1)*W16) with W16 = 3 *
-// 2^(d-1): a node block of 2^(d-1) words (word 0 holds the root in its low
+// The other paths use forms made of a second, compact one whose thresholds
+// have six bits.  A compact tree is 3 * 2^(d-1) words: a node block of 2^(d-1) words (word 0 holds the root in its low
 // half, word p >= 1 holds internal nodes 2p and 2p+1 as the low and high
 // halves) followed by the 2^d leaf values.  A 16-bit node is (f & 3) |
 // min(thr, 63) << 2 | (f >> 2) << 8.
@@ -91,13 +90,10 @@ struct EnsembleDesc {
     int32_t score6;
     int32_t leaf6;
     const uint32_t* words;
-    const uint32_t* words16;
-    // Local forms for the chain-local annealing path: the compact form's
-    // trees re-laid at an odd word stride (the smallest >= the tree's words
-    // that is 1 mod 32), whole trees (local_full) or node blocks only
-    // (local_nodes); zero padded, plus 16 bytes of slack at the end.
+    // Local form for the chain-local annealing path and scoring: the compact
+    // form's whole trees re-laid at an odd word stride (local_stride), zero
+    // padded, plus 16 bytes of slack at the end.
     const uint32_t* local_full;
-    const uint32_t* local_nodes;
     // Split form for walks whose top levels stay in LDS: local_top holds the
     // first 2^(d-2) words of each compact node block (levels 0 .. d-2) at an
     // odd word stride; tail holds per tree and last-level node m (2^(d-1)
@@ -134,6 +130,14 @@ struct ChainMeta {
     float kth_score;
     uint64_t kth_cfg;
 };
+
+// Words between trees of the local forms: whole trees, or tops only (tail);
+// the smallest stride holding one that is 1 mod 32, so that the same word of
+// consecutive trees falls in consecutive LDS banks.
+__host__ __device__ constexpr int local_stride(int depth, bool tail) {
+    const int w = tail ? (depth >= 2 ? 1 << (depth - 2) : 1) : 3 << (depth - 1);
+    return w + ((1 - w) % 32 + 32) % 32;
+}
 
 // Tile byte offset of feature f: quad (f >> 2), byte (f & 3).
 __host__ __device__ inline uint32_t tile_offset(int f) {
@@ -221,10 +225,8 @@ struct at_ensemble_s {
     int device = 0;
     at::EnsembleDesc desc{};
     at::DeviceBuf d_words;
-    at::DeviceBuf d_words16;
     at::DeviceBuf d_words32;
     at::DeviceBuf d_local_full;
-    at::DeviceBuf d_local_nodes;
     at::DeviceBuf d_local_top;
     at::DeviceBuf d_tail;
 };
@@ -321,7 +323,6 @@ struct LocalPlan {
     size_t lds_bytes = 0;
     double round_bytes = 0.0; // bytes streamed per round by one workgroup
 };
-int local_tree_stride(int words);
 bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& ch, LocalPlan& pl);
 hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chains_s& ch, const LocalPlan& pl,
                            int steps, bool init, const float* thr, at_entry* best, at_entry* trace,

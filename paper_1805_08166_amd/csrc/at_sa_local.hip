@@ -64,11 +64,9 @@ struct LocalArgs {
     int n_chunks;
     int resident;             // the ring holds every tree (loaded once); else two chunk buffers
     int walk_waves;           // waves 1 .. walk_waves walk; later waves load
-    int tail;                 // tops resident (local_top), last level and leaves from the tail records
+    int tail;                 // tree tops resident, last level and leaves from the tail records
     const uint4* tail_rec;    // [T][2^(d-1)] records {node, left leaf, right leaf, 0}
-    int gather;               // leaves from global memory (leaf_src) instead of the ring
-    const uint32_t* leaf_src; // compact form: leaves of tree t at leaf_src[t * w16 + 2^(d-1) + q]
-    int w16;
+    int gather;               // tree tops streamed, last level and leaves from the tail records
     // dynamic LDS layout (byte offsets; the feature tile is at 0)
     uint32_t off_ring, ring_bytes;
     uint32_t off_lv;
@@ -91,11 +89,7 @@ __device__ __forceinline__ void load_trees(const LocalArgs& a, uint8_t* dst, int
 }
 
 
-// FAST instances run the single-pass plans with at most four chains per
-// workgroup and full workgroups (the launcher picks them); the others run
-// every other plan.  Compiling the two apart keeps each one's uniform state
-// within the scalar registers.
-template <int TMPL, int DEPTH, bool FAST>
+template <int TMPL, int DEPTH>
 __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
     using N = Nest<TMPL>;
     constexpr int Q = (N::F + 3) / 4;
@@ -231,61 +225,9 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         });
     if (owner && a.steps > 0)
         with_space([&](const SpaceDesc& sd) { draw_move(sd, k0, k1, gchain, a.step0, mv_j, mv_v, mv_radix); });
-    // Fast plans (single pass, at most four chains per workgroup) take the
-    // owners' side work off the path from one fold to the next: a helper
-    // wave draws the moves two steps ahead, and a round's candidates are
-    // offered to the best lists by another wave during the next round's fold
-    // (the offers of a chain stay in round order).  Roles during a fold:
-    // wave 0 folds, waves 1-2 make and evaluate the next candidates, wave 3
-    // offers, wave 4 draws, the last wave brings the next thresholds.  The
-    // chain's record carries, by round parity, the two candidates made for
-    // the round, which of them is the round's (the previous accept's
-    // outcome) and the configuration the round starts from, so that no
-    // reader in one round meets a writer of the same round.
     // single pass: every tree walked in one pass per round (tail mode, or
     // resident trees in one chunk); such runs work a round ahead
-    const bool single = FAST || a.tail || (a.resident && a.n_chunks == 1);
-    const bool fast = FAST;
-    auto draw_into = [&](int j, int st) {
-        // move of step st for chain j into its record (slot st & 1)
-        int jm;
-        uint32_t v;
-        uint64_t radix;
-        const uint32_t gch = (uint32_t)(a.chain0 + (uint64_t)(c0 + j));
-        if (staged) draw_move(s_desc, k0, k1, gch, a.step0 + (uint32_t)st, jm, v, radix);
-        else draw_move(a.descs[space_of(a.offsets, a.n_spaces, c0 + j)], k0, k1, gch, a.step0 + (uint32_t)st, jm, v,
-                       radix);
-        rec[j].mvj[st & 1] = jm;
-        rec[j].mvv[st & 1] = v;
-        rec[j].mvr[st & 1] = radix;
-    };
-    // offer of round rr's candidates (waiting in the records) by the 16-lane
-    // groups of one wave: group g takes chain g
-    auto offer_pending = [&](int rr) {
-        const int g = lane >> 4, gl = lane & 15;
-        const int jc = g < nc ? g : 0;
-        ChainRec& R = rec[jc];
-        const uint64_t pc = R.pcfg[rr & 1];
-        const float ps = R.pscore[rr & 1];
-        const bool first = a.init && rr == 0;
-        const bool q = g < nc && (first || (int)R.count < k || precedes(ps, pc, R.kth_score, R.kth_cfg));
-        if (gl == 0 && g < nc) {
-            R.cfg = pc;
-            R.score = ps;
-        }
-        group_offer(lists + jc * k, R, k, gl, 0xffffull << (16 * g), q);
-    };
-    if (fast && owner) {
-        const int s1 = (a.init ? -1 : 0) + 1;
-        if (s1 < a.steps) draw_into(tid, s1);
-        // round 0 starts from the loaded configuration; its candidate is
-        // outcome 0
-        ChainRec& R = rec[tid];
-#pragma unroll
-        for (int j = 0; j < MAX_KNOBS / 2; ++j) R.curk[0][j] = cur[2 * j] | (cur[2 * j + 1] << 16);
-        R.curcfg[0] = cur_cfg;
-        R.ssel[0] = 0u;
-    }
+    const bool single = a.tail || (a.resident && a.n_chunks == 1);
 
     // Loop gr's features of chain j's configuration nx into row dst.
     auto eval_loop = [&](const uint32_t (&nx)[MAX_KNOBS], int j, int gr_, uint8_t* dst) {
@@ -321,16 +263,6 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         float thr_v = 0.0f;
         if (owner && ahead) {
             thr_v = rec[tid].thr;
-            if (fast) {
-                // the candidate evaluated for this round's outcome
-                const ChainRec& R = rec[tid];
-                const uint32_t os = R.ssel[r & 1] & 1u;
-                uint32_t w[MAX_KNOBS / 2];
-#pragma unroll
-                for (int j = 0; j < MAX_KNOBS / 2; ++j) w[j] = R.snx[r & 1][os][j];
-                unpack(w, cd);
-                cfg = R.scfg[r & 1][os];
-            }
         } else if (owner) {
             cfg = 0;
             if (is_init) {
@@ -351,11 +283,6 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
             }
 #pragma unroll
             for (int j = 0; j < MAX_KNOBS / 2; ++j) rec[tid].nx[j] = cd[2 * j] | (cd[2 * j + 1] << 16);
-            if (fast) {
-#pragma unroll
-                for (int j = 0; j < MAX_KNOBS / 2; ++j) rec[tid].snx[r & 1][0][j] = rec[tid].nx[j];
-                rec[tid].scfg[r & 1][0] = cfg;
-            }
         }
         if (!ahead) {
             lds_barrier();
@@ -383,19 +310,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
             int j = t & (cpb - 1);
             j = j < nc ? j : nc - 1;
             uint32_t w[TU];
-            if (fast) {
-                // 448 fill threads: the words of every pass but the last exist
-                const uint8_t* row = frow + (ahead ? (rec[j].ssel[r & 1] & 1u) * a.frow_stride : 0u) + j * RS;
-                constexpr bool LAST = (TU - 1) * NF_MIN + NF_MIN > Q * 64;   // the last pass is partial
-                const bool last_ok = !LAST || t + (TU - 1) * NF_MIN < Q * 64;
-#pragma unroll
-                for (int u = 0; u < TU; ++u)
-                    if (u + 1 < TU || last_ok)
-                        w[u] = *reinterpret_cast<const uint32_t*>(row + 4 * ((t + u * NF_MIN) >> 6));
-#pragma unroll
-                for (int u = 0; u < TU; ++u)
-                    if (u + 1 < TU || last_ok) tile[t + u * NF_MIN] = (w[u] << 2) | 0x03030303u;
-            } else {
+            {
                 const uint8_t* row = frow + (ahead ? rec[j].sel * a.frow_stride : 0u) + j * RS;
 #pragma unroll
                 for (int u = 0; u < TU; ++u) {
@@ -417,7 +332,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
             // LDS.  Thread t takes chain t % cpb and, with S = min(ceil(T /
             // 4), threads / cpb) slots, slot u = t / cpb < S takes trees u,
             // u + S, u + 2S, u + 3S per pass.
-            if (owner && more && !fast) {
+            if (owner && more) {
                 with_space([&](const SpaceDesc& sd) {
                     draw_move(sd, k0, k1, gchain, a.step0 + (uint32_t)(s + 1), mv_j, mv_v, mv_radix);
                 });
@@ -488,9 +403,6 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
             lds_barrier();
             if (wave == 0) {
                 if (lane < nc) sc = fold_row(sc, lv + lane * a.lv_stride, a.T);
-            } else {
-                if (fast && wave == 3 && r > 0) offer_pending(r - 1);
-                if (fast && wave == 4 && lane < nc && s + 2 < a.steps) draw_into(lane, s + 2);
             }
             if (wave > 0 && more) {
                 if (wave == nthreads / 64 - 1 && lane < nc) rec[lane].thr = a.thr[(c0 + lane) * a.steps + s + 1];
@@ -500,37 +412,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
                     const int gr2 = it & 15, j = (it >> 4) & (cpb - 1), v = (it >> 4) >> cpb_log2;
                     if (j < nc && gr2 < N::L) {
                         uint32_t nx[MAX_KNOBS];
-                        if (fast) {
-                            // the candidate itself: step s + 1's move applied to
-                            // this round's candidate (v = 0; also v = 1 after
-                            // the initial draw, which is always accepted) or to
-                            // the configuration the round started from (v = 1)
-                            ChainRec& R = rec[j];
-                            const int sl = (s + 1) & 1;
-                            const uint32_t os = R.ssel[r & 1] & 1u;
-                            uint32_t w[MAX_KNOBS / 2], base[MAX_KNOBS];
-                            uint64_t bcfg;
-                            if (v == 0 || is_init) {
-#pragma unroll
-                                for (int q = 0; q < MAX_KNOBS / 2; ++q) w[q] = R.snx[r & 1][os][q];
-                                bcfg = R.scfg[r & 1][os];
-                            } else {
-#pragma unroll
-                                for (int q = 0; q < MAX_KNOBS / 2; ++q) w[q] = R.curk[r & 1][q];
-                                bcfg = R.curcfg[r & 1];
-                            }
-                            unpack(w, base);
-                            uint64_t ncfg;
-                            apply_move(base, bcfg, R.mvj[sl], R.mvv[sl], R.mvr[sl], nx, ncfg);
-                            if (gr2 == 0) {
-#pragma unroll
-                                for (int q = 0; q < MAX_KNOBS / 2; ++q)
-                                    R.snx[(r + 1) & 1][v][q] = nx[2 * q] | (nx[2 * q + 1] << 16);
-                                R.scfg[(r + 1) & 1][v] = ncfg;
-                            }
-                        } else {
-                            unpack(v ? rec[j].nxb : rec[j].nx, nx);
-                        }
+                        unpack(v ? rec[j].nxb : rec[j].nx, nx);
                         eval_loop(nx, j, gr2, frow + v * a.frow_stride + j * RS);
                     }
                 }
@@ -540,7 +422,9 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         // walkers walk chunk it and write its leaf values (leaves gathered
         // from global memory are written one iteration later); wave 0 folds
         // chunk it - lag.
-        uint32_t vprev[4] = {0u, 0u, 0u, 0u};
+        uint4 rprev[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) rprev[g] = make_uint4(0u, 0u, 0u, 0u);
         int tprev[4] = {-1, -1, -1, -1};
         for (int it = 0; it < nck + lag; ++it) {
             const int gc = r * nck + it;
@@ -570,21 +454,27 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
                         ti[g] = tl < nt ? tl : -1;
                         nb[g] = rb + (uint32_t)(tl < nt ? tl : u) * (uint32_t)a.ts * 4u;
                     }
-                    walk4_local<DEPTH>(nb, fb, q);
+                    if (a.gather) walk4_local<(DEPTH >= 2 ? DEPTH - 1 : 1)>(nb, fb, q);
+                    else walk4_local<DEPTH>(nb, fb, q);
                 }
                 if (a.gather) {
-                    // the leaf values gathered last iteration, then this chunk's
+                    // the last levels from the records gathered last
+                    // iteration, then this chunk's records
                     if (it > 0 && jw < nc) {
                         float* lvk = lv + ((it - 1) & 1) * a.ct + jw * a.lv_stride;
 #pragma unroll
-                        for (int g = 0; g < 4; ++g)
-                            if (tprev[g] >= 0) lvk[tprev[g]] = __uint_as_float(vprev[g]);
+                        for (int g = 0; g < 4; ++g) {
+                            const uint32_t node = rprev[g].x;
+                            const uint32_t x4 = lds[((node & LOCAL_TILE_MASK) | fb) - lbase];
+                            const uint32_t v = x4 >= (node & 0xffu) ? rprev[g].z : rprev[g].y;
+                            if (tprev[g] >= 0) lvk[tprev[g]] = __uint_as_float(v);
+                        }
                     }
                     if (walks) {
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
                             const int tt = ti[g] >= 0 ? ti[g] : u;
-                            vprev[g] = a.leaf_src[(size_t)(t0 + tt) * a.w16 + (NBB / 4) + q[g]];
+                            rprev[g] = a.tail_rec[((size_t)(t0 + tt) << (DEPTH - 1)) + q[g]];
                         }
                     }
 #pragma unroll
@@ -613,41 +503,6 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         }
         // (5) offer to the best list when some chain qualifies, then the
         // Metropolis test
-        if (fast) {
-            // only the outcome is needed before the barrier (the next round's
-            // tile copy reads it); in tail mode the rest of the owner's books
-            // follow it, beside the other waves' copy (in the resident mode
-            // wave 0 walks first, so they stay ahead of it)
-            const bool acc = owner && (is_init || (sc - cur_s) >= thr_v);
-            if (owner) rec[tid].ssel[(r + 1) & 1] = acc ? 0u : 1u;
-            auto books = [&]() {
-                if (!is_init && a.trace) {
-                    at_entry tr;
-                    tr.cfg = cfg;
-                    tr.score = sc;
-                    tr.flag = acc ? 1u : 0u;
-                    a.trace[c * a.steps + s] = tr;
-                }
-                // the candidate waits for its offer (wave 3, next round); the
-                // next round starts from the configuration published here
-                ChainRec& R = rec[tid];
-                R.pcfg[r & 1] = cfg;
-                R.pscore[r & 1] = sc;
-                if (acc) {
-#pragma unroll
-                    for (int j = 0; j < MAX_KNOBS; ++j) cur[j] = cd[j];
-                    cur_s = sc;
-                    cur_cfg = cfg;
-                }
-#pragma unroll
-                for (int j = 0; j < MAX_KNOBS / 2; ++j) R.curk[(r + 1) & 1][j] = cur[2 * j] | (cur[2 * j + 1] << 16);
-                R.curcfg[(r + 1) & 1] = cur_cfg;
-            };
-            if (owner && !a.tail) books();
-            lds_barrier();
-            if (owner && a.tail) books();
-            continue;
-        }
         if (owner) {
             ChainRec& R = rec[tid];
             const bool qual = is_init || (int)R.count < k || precedes(sc, cfg, R.kth_score, R.kth_cfg);
@@ -690,11 +545,6 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         }
     }
 
-    // the last round's offer, once the owners have recorded its candidates
-    if (fast && rounds > 0) {
-        lds_barrier();
-        if (wave == 3) offer_pending(rounds - 1);
-    }
     // write the chain state and the best lists back
     __syncthreads();
     if (owner) {
@@ -713,13 +563,13 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
     }
 }
 
-template <int TMPL, bool FAST>
+template <int TMPL>
 hipError_t launch_local_t(const LocalArgs& a, int depth, int grid, int threads, size_t lds, hipStream_t stream,
                           hipEvent_t start, hipEvent_t stop) {
     const void* fn = nullptr;
     switch (depth) {
 #define AT_LOCAL_CASE(D) \
-    case D: fn = reinterpret_cast<const void*>(&k_local<TMPL, D, FAST>); break;
+    case D: fn = reinterpret_cast<const void*>(&k_local<TMPL, D>); break;
         AT_LOCAL_CASE(1) AT_LOCAL_CASE(2) AT_LOCAL_CASE(3) AT_LOCAL_CASE(4) AT_LOCAL_CASE(5) AT_LOCAL_CASE(6)
         AT_LOCAL_CASE(7) AT_LOCAL_CASE(8) AT_LOCAL_CASE(9) AT_LOCAL_CASE(10) AT_LOCAL_CASE(11) AT_LOCAL_CASE(12)
 #undef AT_LOCAL_CASE
@@ -750,9 +600,6 @@ hipError_t launch_local_t(const LocalArgs& a, int depth, int grid, int threads, 
 
 }  // namespace
 
-// Smallest word stride >= words that is 1 mod 32.
-int local_tree_stride(int words) { return words + ((1 - words) % 32 + 32) % 32; }
-
 // Plan of the chain-local path for a run, or false when it does not fit.
 // Workgroups of 512 threads: wave 0 folds and keeps the books, then walker
 // waves (a slot per chain and up to four trees per slot and chunk), then
@@ -764,7 +611,6 @@ bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& 
     const int64_t n = ch.n_chains;
     const int Q = (sp.descs[0].n_features + 3) / 4;
     const int d = e.depth;
-    const int NB = 1 << (d - 1), NL = 1 << d;
     const int T = e.n_trees;
     int n_cu = 256;
     (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ch.device);
@@ -787,7 +633,7 @@ bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& 
                          al16((size_t)cpb * RS) + 16 + al16(sizeof(SpaceDesc) + (size_t)fac_max * 8);
     if (tile + fixed >= LOCAL_LDS_BYTES) return false;
     const size_t avail = LOCAL_LDS_BYTES - tile - fixed;
-    const int ts_full = local_tree_stride(NB + NL), ts_nodes = local_tree_stride(NB);
+    const int ts_full = local_stride(d, false), ts_top = local_stride(d, true);
     auto lv_bytes = [&](int ct) { return al16((size_t)cpb * (2 * (size_t)ct + 4) * 4); };
     pl = LocalPlan{};
     pl.cpb = cpb;
@@ -804,7 +650,6 @@ bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& 
     // tail: the tree tops (levels 0 .. d-2) resident, every tree walked in
     // one pass with the last level and leaf read from the tail records;
     // needs one row of leaf values per chain for all trees
-    const int ts_top = local_tree_stride(d >= 2 ? NB / 2 : 1);
     const size_t top_bytes = al16((size_t)T * ts_top * 4);
     const int T4 = (T + 3) / 4 * 4;
     const size_t lv_all = al16((size_t)cpb * ((size_t)T4 + 4) * 4);
@@ -825,12 +670,13 @@ bool plan_local(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& 
     } else {
         // streamed in chunks through two buffers.  Leaves are gathered from
         // global memory when that moves fewer bytes per round than streaming
-        // them (a 64-byte line per chain and tree against the leaf block).
+        // them (a 64-byte line per chain and tree against the last level and
+        // the leaf block).
         const double stream_full = (double)T * ts_full * 4;
-        const double stream_nodes = (double)T * ts_nodes * 4 + (double)cpb * T * 64;
+        const double stream_tops = (double)T * ts_top * 4 + (double)cpb * T * 64;
         pl.resident = 0;
-        pl.gather = stream_nodes < stream_full ? 1 : 0;
-        pl.ts = pl.gather ? ts_nodes : ts_full;
+        pl.gather = d >= 2 && stream_tops < stream_full ? 1 : 0;
+        pl.ts = pl.gather ? ts_top : ts_full;
         // per tree of a chunk: two ring copies and two leaf-value slots per chain
         const size_t per_tree = 8 * ((size_t)pl.ts + cpb);
         const size_t spare = avail > (size_t)cpb * 16 + 64 ? avail - (size_t)cpb * 16 - 64 : 0;
@@ -914,7 +760,7 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     a.thr = thr;
     a.trace = trace;
     a.best = best;
-    a.tw = pl.tail ? e.local_top : (pl.gather ? e.local_nodes : e.local_full);
+    a.tw = (pl.tail || pl.gather) ? e.local_top : e.local_full;
     a.ts = pl.ts;
     a.T = e.n_trees;
     a.ct = pl.ct;
@@ -923,8 +769,6 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     a.tail = pl.tail;
     a.tail_rec = e.tail;
     a.gather = pl.gather;
-    a.leaf_src = e.words16;
-    a.w16 = 3 << (e.depth - 1);
     a.off_ring = pl.off_ring;
     a.ring_bytes = pl.ring_bytes;
     a.off_lv = pl.off_lv;
@@ -939,16 +783,9 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     ch.events_used[0] = ch.events_used[1] = 0;
     hipEvent_t start = nullptr, stop = nullptr;
     if ((err = next_events(ch, 0, start, stop)) != hipSuccess) return err;
-    const bool fast = (pl.tail || (pl.resident && pl.n_chunks == 1)) && pl.cpb <= 4 && pl.threads == LOCAL_WG_MAX;
     if (sp.tmpl == AT_TMPL_GEMM)
-        return fast ? launch_local_t<AT_TMPL_GEMM, true>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream, start,
-                                                         stop)
-                    : launch_local_t<AT_TMPL_GEMM, false>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream, start,
-                                                          stop);
-    return fast ? launch_local_t<AT_TMPL_CONV2D_NCHW, true>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream,
-                                                            start, stop)
-                : launch_local_t<AT_TMPL_CONV2D_NCHW, false>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream,
-                                                             start, stop);
+        return launch_local_t<AT_TMPL_GEMM>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream, start, stop);
+    return launch_local_t<AT_TMPL_CONV2D_NCHW>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream, start, stop);
 }
 
 }  // namespace at
