@@ -14,13 +14,21 @@ namespace at {
 namespace {
 thread_local std::string g_last_error;
 
-// Bytes one workgroup of the chain-local path may stream per step for the
-// path to be chosen by default.  Measured on MI355X: the chain-local path
-// wins with its ensemble resident in LDS (GEMM 512^3: 2.5 ms against 6.4 ms
-// per run) and streaming about 0.4 MB per step (conv2d C2: 5.7 against
-// 9.2 ms), and loses at 1.5 MB per step (twelve conv2d workloads: 33 against
-// 20 ms).
-constexpr double LOCAL_AUTO_BYTES = 768.0 * 1024;
+// Whether a run takes the chain-local path by default.  With its ensemble in
+// LDS (whole, or the tree tops with the rest read from the L2) the path wins
+// up to 768 KB of tail records a step and workgroup.  Streamed plans are
+// bound by their chunks (1.1-1.8 us each); the tree-partitioned path by two
+// launches and the fold, whatever the chains (11-25 us a step below 4096
+// chains).  Both measured over 16 .. 4096 chains, 50 .. 2000 trees, depths 4
+// .. 10: 11 chunks of 184 trees for four chains a workgroup take 22.0 us
+// against 25.0 (depth 8, 2000 trees, 1024 chains); 11 chunks for eight 21.0
+// against 19.4 (1000 trees, 2048 chains); 21 chunks for sixteen 26.7 against
+// 22.6 (depth 4, 1000 trees, 4096 chains).
+bool local_by_default(const LocalPlan& pl) {
+    if (pl.resident || pl.tail) return pl.round_bytes <= 768.0 * 1024;
+    const int most = pl.cpb <= 4 ? 13 : (pl.cpb == 8 ? 8 : 5);
+    return pl.n_chunks <= most && pl.round_bytes <= 1100.0 * 1000;
+}
 
 template <class T>
 at_status upload(DeviceBuf& buf, const T* host, size_t count) {
@@ -912,14 +920,13 @@ static at_status sa_run_impl(at_space_t space, at_ensemble_t ens, at_ensemble_t 
         return fail(AT_E_UNSUPPORTED, f + ": step counter must fit 32 bits");
     DeviceGuard g(chains->device);
     const bool init = !chains->initialised;
-    // path: chain-local when its plan fits and one workgroup streams at most
-    // LOCAL_AUTO_BYTES per step, else tree-partitioned; Eq. 4 runs take the
-    // tree-partitioned path
+    // path: chain-local when its plan fits and is the faster one, else
+    // tree-partitioned; Eq. 4 runs take the tree-partitioned path
     LocalPlan pl;
     const bool local_fits = !global && chains->n_chains > 0 && plan_local(*space, ens->desc, *chains, pl);
     int path = chains->path;
     if (path == AT_SA_PATH_AUTO)
-        path = (local_fits && pl.round_bytes <= LOCAL_AUTO_BYTES) ? AT_SA_PATH_LOCAL : AT_SA_PATH_TREES;
+        path = (local_fits && local_by_default(pl)) ? AT_SA_PATH_LOCAL : AT_SA_PATH_TREES;
     if (path == AT_SA_PATH_LOCAL && global)
         return fail(AT_E_UNSUPPORTED, f + ": two-model (Eq. 4) runs take the tree-partitioned path");
     if (path == AT_SA_PATH_LOCAL && chains->n_chains > 0 && !local_fits)
