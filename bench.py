@@ -67,7 +67,8 @@ def tree_eval_bytes(depth: int) -> int:
 
 
 KERNEL_SOURCES = {"k_trees": os.path.join(ROOT, "paper_1805_08166_amd", "csrc", "at_sa_tp.hip"),
-                  "k_local": os.path.join(ROOT, "paper_1805_08166_amd", "csrc", "at_sa_local.hip")}
+                  "k_local": os.path.join(ROOT, "paper_1805_08166_amd", "csrc", "at_sa_local.hip"),
+                  "k_single": os.path.join(ROOT, "paper_1805_08166_amd", "csrc", "at_sa_single.hip")}
 COPY_BYTES = 256 << 20
 
 
@@ -196,7 +197,7 @@ def bench_sa(P, name, steps, warmup, transfer=False):
     wall = time.perf_counter() - t0
     t = float(np.mean(ev))
     # one more run, profiled: average launch durations of the kernels.  The
-    # walk kernel is k_local on the chain-local path (one launch per run, a
+    # walk kernel is k_single or k_local on the chain-local path (one launch per run, a
     # scoring round per step) and k_trees on the tree-partitioned path (one
     # launch per scoring round).
     P.at_sa_set_profiling(w.chains, True)
@@ -205,6 +206,10 @@ def bench_sa(P, name, steps, warmup, transfer=False):
     P.at_sa_set_profiling(w.chains, False)
     local = P.at_chains_last_path(w.chains) == P.AT_SA_PATH_LOCAL
     plan = P.at_chains_last_plan(w.chains)
+    walk = "k_trees"
+    if local:
+        # the ensemble in LDS and at most four chains a workgroup: k_single
+        walk = "k_single" if plan["chunks"] == 0 and plan["chains_per_wg"] <= 4 else "k_local"
     tree_s = kt["tree_ms"] / kt["tree_launches"] * 1e-3
     rounds_per_launch = w.steps if local else 1
     tree_bytes = w.n * w.wl["trees"] * rounds_per_launch * tree_eval_bytes(w.wl["depth"])
@@ -213,7 +218,7 @@ def bench_sa(P, name, steps, warmup, transfer=False):
         name += f"{w.wl['trees']} trees depth {w.wl['depth']} each; two tree launches per step)"
     return w, dict(
         path="chain-local" if local else "tree-partitioned", plan=plan,
-        walk_kernel="k_local" if local else "k_trees",
+        walk_kernel=walk,
         workload=describe(name.split(" ")[0]) + name[len(name.split(" ")[0]):], ms_per_run=t * 1e3, ms_min=float(np.min(ev)) * 1e3, wall_s=wall,
         evals_per_s=w.evals / t, tree_evals_per_s=w.tree_evals / t,
         run_lds_bytes=w.lds_bytes, run_lds_TBps=w.lds_bytes / t / 1e12,

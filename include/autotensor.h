@@ -414,10 +414,10 @@ at_status at_chains_last_path(at_chains_t chains, int* path);
  * Chain-local run: info[0] chains per workgroup, [1] threads per workgroup,
  * [2] workgroups, [3] trees per chunk, [4] chunks streamed per step (0:
  * nothing is streamed), [5] how leaves are reached: 0 from LDS (whole trees
- * resident or streamed), 1 streamed node blocks with leaves read from
- * global memory, 2 tree tops resident in LDS with the last level and its
- * leaves read from global memory, [6] dynamic LDS bytes, [7] bytes one
- * workgroup reads per step from outside its LDS.
+ * resident or streamed), 1 tree tops streamed, 2 tree tops resident in LDS
+ * (1 and 2 read the last level and its leaves from global memory), [6]
+ * dynamic LDS bytes, [7] bytes one workgroup reads per step from outside its
+ * LDS.
  * Tree-partitioned run: info[0] trees per tree-kernel workgroup, [1] waves
  * per tree-kernel workgroup, [2] tree-kernel workgroups, [3] chain slices
  * per tree group, [4] 64-chain blocks per slice (a wave walks more than one

@@ -69,10 +69,11 @@ constexpr int STAGE_CHAINS = 16;         // chains per chain-kernel workgroup
 // 2^d .. 2^(d+1)-1 hold the leaf values (float bits); word 0 is unused.
 //
 // The other paths use forms made of a second, compact one whose thresholds
-// have six bits.  A compact tree is 3 * 2^(d-1) words: a node block of 2^(d-1) words (word 0 holds the root in its low
-// half, word p >= 1 holds internal nodes 2p and 2p+1 as the low and high
-// halves) followed by the 2^d leaf values.  A 16-bit node is (f & 3) |
-// min(thr, 63) << 2 | (f >> 2) << 8.
+// have six bits.  A compact tree is 3 * 2^(d-1) words: a node block of
+// 2^(d-1) words (word 0 holds the root in its low half, word p >= 1 holds
+// internal nodes 2p and 2p+1 as the low and high halves) followed by the
+// 2^d leaf values.  A 16-bit node is (f & 3) | min(thr, 63) << 2 |
+// (f >> 2) << 8.
 //   - Annealing features are loop-context bitlens, never above 31, so a
 //     split on x < thr decides the same with thr clamped to 63.
 //   - Batched scoring takes any feature values: with x clamped to 63 the

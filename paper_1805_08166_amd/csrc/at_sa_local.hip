@@ -20,8 +20,12 @@
 // Tree layout in the ring ("local form"): tree t occupies `ts` words, the
 // compact node block (2^(d-1) words) followed, when leaves are streamed, by
 // the 2^d leaf values; ts is odd, so the same node word of consecutive
-// trees falls in consecutive LDS banks.  With `gather` set only node
-// blocks are streamed and each walk reads its one leaf from global memory.
+// trees falls in consecutive LDS banks.  With `tail` (resident) or `gather`
+// (streamed) set the ring holds tree tops only, and each walk reads its last
+// level and both its leaves as one 16-byte tail record from global memory.
+//
+// Plans with the whole ensemble in LDS and at most four chains a workgroup
+// run k_single instead (at_sa_single.hip).
 #include <hip/hip_ext.h>
 
 #include "at_chain.h"

@@ -47,9 +47,10 @@ constexpr int CPW = 16;                 // chains per chain-kernel workgroup
 static_assert(CPW == 16 && CPW == STAGE_CHAINS, "a chain-kernel workgroup reads one 16-chain block of V");
 constexpr int FOLD_P = 32;              // 4-tree groups per fold pass: 32 x 16 chains x 16 B = 8 KB
 // Passes in the LDS ring: one model's fold keeps one pass in flight while
-// it adds the other (deeper rings measured slower: C12 chain kernel 16.3 us
-// with two passes, 16.6 with three, 16.7 with four, 17.1 with six); Eq. 4's
-// two folds take a pass of each at a time and keep a pair in flight.
+// it adds the other (deeper rings measured slower: C12 chain kernel 15.5 us
+// with two passes, and 16.3, 16.6, 16.7 and 17.1 with two, three, four and
+// six in an earlier form of the kernel); Eq. 4's two folds take a pass of
+// each at a time and keep a pair in flight.
 constexpr int FOLD_R1 = 2;
 constexpr int FOLD_R2 = 4;
 constexpr size_t PASS_BYTES = (size_t)FOLD_P * CPW * 16;
