@@ -7,6 +7,7 @@
 //            thresholds above six bits, of 28, 44 or 48 feature quads (GEMM
 //            and conv2d loop-context rows, relation rows)
 #include <algorithm>
+#include <atomic>
 
 #include "at_chain.h"
 
@@ -373,15 +374,19 @@ constexpr size_t SCORE_LDS_BYTES = 163840 - 1024;
 
 // The walks address the tile with an and-or, which needs the dynamic LDS
 // block at address 0: no static LDS in the kernel.  Raises the kernel's
-// dynamic LDS limit, once per kernel.
-hipError_t configure(const void* fn, bool& done) {
-    if (done) return hipSuccess;
+// dynamic LDS limit, once per kernel and device (a bit of `done` each).
+hipError_t configure(const void* fn, std::atomic<uint64_t>& done) {
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = device < 64 ? (uint64_t)1 << device : 0;
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
     hipFuncAttributes fa;
-    hipError_t e = hipFuncGetAttributes(&fa, fn);
+    e = hipFuncGetAttributes(&fa, fn);
     if (e != hipSuccess) return e;
     if (fa.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCORE_LDS_BYTES);
-    if (e == hipSuccess) done = true;
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
     return e;
 }
 
@@ -446,7 +451,7 @@ bool plan_rows(const EnsembleDesc& e, int64_t n, RowsPlan& pl, RowsArgs& a) {
 
 template <int DEPTH>
 hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream) {
-    static bool done[2] = {false, false};
+    static std::atomic<uint64_t> done[2];
     constexpr bool TAILS = DEPTH >= 2;
     const bool tail = TAILS && pl.tail;
     const void* fn = tail ? reinterpret_cast<const void*>(&k_rows<DEPTH, TAILS>)
@@ -462,6 +467,17 @@ hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream)
 hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
                         bool accumulate, hipStream_t stream) {
     if (n == 0) return hipSuccess;
+    // A launch holds at most 2^32 threads, and k_rows takes four to 128 a
+    // row: larger calls are cut into pieces (2^28 rows keep a piece's rows as
+    // aligned as the call's).
+    constexpr int64_t PIECE = (int64_t)1 << 28;
+    for (; n > PIECE; n -= PIECE) {
+        const hipError_t err = launch_score(e, feats, PIECE, scores, leaves, accumulate, stream);
+        if (err != hipSuccess) return err;
+        feats += PIECE * e.n_features;
+        scores += PIECE;
+        if (leaves) leaves += PIECE * e.n_trees;
+    }
     const bool vec = e.n_features % 4 == 0 && (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
     RowsPlan pl;
     RowsArgs a{};

@@ -107,3 +107,22 @@ def test_scores_at_the_six_bit_edge(P):
         thr = r.integers(60, top + 1, size=thr.shape).astype(np.uint8)
         check(P, (fid, thr, leaf), f, True)
         check(P, (fid, thr, leaf), f, False)
+
+
+def test_scores_of_more_rows_than_one_launch_takes(P):
+    """2^29 rows and some: eight threads a row would be more than the 2^32
+    threads of one launch.  One feature, so the oracle's scores of its 64
+    values give every row's."""
+    import torch
+    n, part = (1 << 29) + 77, 1 << 26
+    print(f"[gpu-score] n {n}", flush=True)
+    tables = W.make_ensemble(28, 2, 1, 6)
+    want = oracle.predict(*tables, np.arange(64, dtype=np.int32)[:, None], False)
+    want = torch.from_numpy(np.asarray(want[0] if isinstance(want, tuple) else want, np.float32)).to(DEV)
+    assert want.unique().numel() > 1
+    ens = P.at_ensemble_create(*tables, 1)
+    f = torch.randint(0, 64, (n, 1), dtype=torch.int32, device=DEV)
+    sc = torch.full((n,), 7.0, dtype=torch.float32, device=DEV)
+    P.at_gbt_predict(ens, f, sc, None)
+    for lo in range(0, n, part):
+        assert torch.equal(sc[lo: lo + part], want[f[lo: lo + part, 0].long()])
