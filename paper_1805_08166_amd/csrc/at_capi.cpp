@@ -14,20 +14,15 @@ namespace at {
 namespace {
 thread_local std::string g_last_error;
 
-// Whether a run takes the chain-local path by default.  With its ensemble in
-// LDS (whole, or the tree tops with the rest read from the L2) the path wins
-// up to 768 KB of tail records a step and workgroup.  Streamed plans are
-// bound by their chunks (1.1-1.8 us each); the tree-partitioned path by two
-// launches and the fold, whatever the chains (11-25 us a step below 4096
-// chains).  Both measured over 16 .. 4096 chains, 50 .. 2000 trees, depths 4
-// .. 10: 11 chunks of 184 trees for four chains a workgroup take 22.0 us
-// against 25.0 (depth 8, 2000 trees, 1024 chains); 11 chunks for eight 21.0
-// against 19.4 (1000 trees, 2048 chains); 21 chunks for sixteen 26.7 against
-// 22.6 (depth 4, 1000 trees, 4096 chains).
-bool local_by_default(const LocalPlan& pl) {
-    if (pl.resident || pl.tail) return pl.round_bytes <= 768.0 * 1024;
-    const int most = pl.cpb <= 4 ? 13 : (pl.cpb == 8 ? 8 : 5);
-    return pl.n_chunks <= most && pl.round_bytes <= 1100.0 * 1000;
+// Whether a run takes the chain-local path by default: up to 768 KB a step
+// and workgroup from outside its LDS.  A plan that streams tree tops counts
+// its whole node blocks: at 642 KB of tops (500 trees of depth 10, 1024
+// chains) it takes 16.5 us a step and the tree-partitioned path 13.3, at 578
+// KB 15.3 and 13.6.
+bool local_by_default(const LocalPlan& pl, const EnsembleDesc& e) {
+    double bytes = pl.round_bytes;
+    if (pl.gather && e.depth >= 2) bytes += 4.0 * e.n_trees * (1 << (e.depth - 2));
+    return bytes <= 768.0 * 1024;
 }
 
 template <class T>
@@ -926,7 +921,7 @@ static at_status sa_run_impl(at_space_t space, at_ensemble_t ens, at_ensemble_t 
     const bool local_fits = !global && chains->n_chains > 0 && plan_local(*space, ens->desc, *chains, pl);
     int path = chains->path;
     if (path == AT_SA_PATH_AUTO)
-        path = (local_fits && local_by_default(pl)) ? AT_SA_PATH_LOCAL : AT_SA_PATH_TREES;
+        path = (local_fits && local_by_default(pl, ens->desc)) ? AT_SA_PATH_LOCAL : AT_SA_PATH_TREES;
     if (path == AT_SA_PATH_LOCAL && global)
         return fail(AT_E_UNSUPPORTED, f + ": two-model (Eq. 4) runs take the tree-partitioned path");
     if (path == AT_SA_PATH_LOCAL && chains->n_chains > 0 && !local_fits)
