@@ -318,12 +318,17 @@ __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __
     if (row < n) scores[row] = accumulate ? scores[row] + acc : acc;
 }
 
+// Alignment in bytes that every feature row has: 16, 8 or 4.
+int row_align(const EnsembleDesc& e, const int32_t* feats) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(feats) | ((uintptr_t)e.n_features * 4u);
+    return at % 16u == 0 ? 16 : (at % 8u == 0 ? 8 : 4);
+}
+
 template <int DEPTH, int SQ>
 hipError_t score_q(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
                    bool accumulate, hipStream_t stream) {
     const unsigned grid = (unsigned)((n + SWG - 1) / SWG);
-    const uintptr_t at = reinterpret_cast<uintptr_t>(feats) | ((uintptr_t)e.n_features * 4u);
-    const int align = at % 16u == 0 ? 16 : (at % 8u == 0 ? 8 : 4);
+    const int align = row_align(e, feats);
     if (leaves)
         hipLaunchKernelGGL((k_score<DEPTH, true, SQ>), dim3(grid), dim3(SWG), 0, stream, e, feats, n, scores, leaves,
                            accumulate ? 1 : 0, align);
@@ -462,6 +467,33 @@ hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream)
     return hipLaunchKernel(fn, dim3((unsigned)((a.n + pl.R - 1) / pl.R)), dim3(pl.waves * 64), args, pl.lds, stream);
 }
 
+// Whether a call that both kernels take goes to k_score.  Measured on rows of
+// 110, 176 and 192 features, k_rows -> k_score:
+//  - Scores: from 131072 rows (two workgroups a compute unit) for trees of up
+//    to eight levels: 2^20 rows of 176 features x 1000 trees of depth 8 take
+//    1.75 ms against 2.3; at 131072 the two are even (148 and 143 us for 500
+//    trees).  Deeper trees leave a lane one or two trees in flight (depth 10,
+//    131072 rows: 307 against 237 us).
+//  - With leaf indices: k_rows' lanes store eight bytes of a row at a time,
+//    all over the rows of a workgroup, which costs more than the walk from 64
+//    rows a workgroup on; a k_score lane goes along its own row.  131072 rows
+//    x 250 trees: depth 4 159 -> 77 us, depth 8 171 -> 115; depth 8, 500
+//    trees: 32769 rows 103 -> 133, 49153 137 -> 135.  The line rises with the
+//    depth; few trees (depth 8, 20: even from 32769 rows; depth 9, 20: 131072
+//    rows 32 -> 27) cross earlier.  Rows on 4-byte boundaries cost k_score
+//    the more to load (131072 rows x 100 trees of depth 7: 101 -> 71, but
+//    200003 x 20 of depth 5: 82 -> 88).
+bool one_lane_a_row(const EnsembleDesc& e, const int32_t* feats, int64_t n, bool leaves) {
+    const int quads = (e.n_features + 3) / 4, d = e.depth;
+    if (quads != 28 && quads != 44 && quads != 48) return false;
+    if (!leaves) return n >= 131072 && d <= 8;
+    const bool few = (int64_t)e.n_trees * d * d <= 4000;
+    const int64_t from = d <= 4 ? 24577 : d <= 6 ? 28673 : d == 7 || (d == 8 && few) ? 36865 : d == 8 ? 49153 : 98305;
+    if (d > 9 || (d == 9 && !few)) return false;
+    if (row_align(e, feats) < 8) return !few && n >= 98305;
+    return n >= from;
+}
+
 }  // namespace
 
 hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
@@ -481,13 +513,7 @@ hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, 
     const bool vec = e.n_features % 4 == 0 && (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
     RowsPlan pl;
     RowsArgs a{};
-    // From 131072 rows (two workgroups a compute unit) one lane a row is the
-    // faster way for trees of up to eight levels: 2^20 rows of 176 features
-    // x 1000 trees of depth 8 take 1.75 ms against 2.3; at 131072 the two are
-    // even (148 and 143 us for 500 trees).  Deeper trees leave it one or two
-    // trees in flight a lane (depth 10, 131072 rows: 307 against 237 us).
-    const int quads = (e.n_features + 3) / 4;
-    if (n >= 131072 && e.depth <= 8 && !leaves && (quads == 28 || quads == 44 || quads == 48))
+    if (one_lane_a_row(e, feats, n, leaves != nullptr))
         return launch_score_wide(e, feats, n, scores, leaves, accumulate, stream);
     if (!plan_rows(e, n, pl, a)) return hipErrorInvalidConfiguration;
     a.feats = feats;
