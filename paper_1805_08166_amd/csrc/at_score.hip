@@ -177,6 +177,11 @@ __global__ __launch_bounds__(1024) void k_rows(RowsArgs a) {
 // k_score: 256 rows a workgroup on the 32-bit node words.
 // ==========================================================================
 
+// Four features, on any 4-byte boundary.
+struct __attribute__((packed, aligned(4))) Quad {
+    int x, y, z, w;
+};
+
 template <int DEPTH> struct ScoreShape {
     static constexpr int W = 2 << DEPTH;                       // words per tree
     static constexpr int CW = DEPTH <= 10 ? 2048 : (DEPTH == 11 ? 4096 : 8192);   // words per chunk
@@ -211,16 +216,14 @@ __device__ __forceinline__ void walk_add_rest(const uint8_t* L, int t, int r, ui
     if constexpr (H > 1) walk_add_rest<DEPTH, H / 2, LEAVES>(L, t, r, fb, acc, lrow, t0);
 }
 
-// SQ: feature quads of a row (28, 44 or 48); align: the rows' alignment in
-// bytes (16, 8 or 4; above 4 only when a row is a multiple of it);
-// accumulate: add the score to the value already in scores (fp32, that value
-// first) instead of storing it.  Bytes past the last feature are never read.
+// SQ: feature quads of a row (28, 44 or 48); accumulate: add the score to the
+// value already in scores (fp32, that value first) instead of storing it.
+// Bytes past the last feature are never read.
 template <int DEPTH, bool LEAVES, int SQ>
 __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __restrict__ feats, int64_t n,
                                                float* __restrict__ scores, uint16_t* __restrict__ leaves,
-                                               int accumulate, int align) {
+                                               int accumulate) {
     using S = ScoreShape<DEPTH>;
-    constexpr int PK = SQ % 11 == 0 ? 11 : (SQ % 12 == 0 ? 12 : 14);   // quads loaded together
     constexpr uint32_t TB = (uint32_t)S::W * 4u;
     __shared__ uint32_t lds[S::CW + SQ * SWG];
     const uint8_t* L = reinterpret_cast<const uint8_t*>(lds);
@@ -230,7 +233,10 @@ __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __
     const int64_t row = (int64_t)blockIdx.x * SWG + tid;
     const uint4* src = reinterpret_cast<const uint4*>(e.words);
 
-    // first chunk in flight while the feature row is packed into the tile
+    const int F = e.n_features;
+    // (the arguments in one round trip)
+    asm volatile("" ::"s"(F), "s"(feats), "s"(n), "s"(src));
+    // first chunk in flight while the feature rows are packed into the tile
     uint32_t pre[S::PER * 4];
 #pragma unroll
     for (int u = 0; u < S::PER; ++u) {
@@ -238,50 +244,42 @@ __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __
         pre[4 * u] = x.x; pre[4 * u + 1] = x.y; pre[4 * u + 2] = x.z; pre[4 * u + 3] = x.w;
     }
     {
-        // rows past the end repeat the last row; their results are not stored
-        const int64_t r = row < n ? row : n - 1;
-        const int F = e.n_features;
-        const int32_t* fr = feats + r * F;
-        uint32_t packed[SQ];
-        auto pack = [](int x, int y, int z, int w) {
-            const uint32_t b0 = (uint32_t)min(max(x, 0), 255), b1 = (uint32_t)min(max(y, 0), 255);
-            const uint32_t b2 = (uint32_t)min(max(z, 0), 255), b3 = (uint32_t)min(max(w, 0), 255);
-            return b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
+        // A wave packs its 64 rows, 16 at a time: a load takes four quads of
+        // each, 64 bytes in one piece (rows are 4-byte aligned), and the next
+        // 16 rows are on their way while these are packed.  Rows past the end
+        // repeat the last row; their results are not stored.  With a lane on
+        // each row a load touched 64 lines, which left the first-level cache
+        // before their next piece was asked for, in three forms by the rows'
+        // alignment: 2^20 rows of 192 features x 200 trees of depth 6 took
+        // 358 us against 317, of 176 x 500 of depth 8 874 against 834, of 110
+        // x 100 of depth 4 199 against 92.
+        constexpr int QG = SQ / 4;
+        const int lane = tid & 63, q0 = lane >> 4;
+        auto byte = [](int x) { return (uint32_t)min(max(x, 0), 255); };
+        // a row that ends within its last quad gives its last four features
+        // there, moved down to their places
+        const int last = min(16 * (QG - 1) + 4 * q0, F - 4) - 4 * q0, down = 8 * (16 * (QG - 1) - last);
+        Quad v[2][QG];
+        auto load = [&](int rg) {
+            const int64_t at = (int64_t)blockIdx.x * SWG + (tid & ~63) + rg * 16 + (lane & 15);
+            const int32_t* fr = feats + (at < n ? at : n - 1) * F + 4 * q0;
+#pragma unroll
+            for (int g = 0; g + 1 < QG; ++g) v[rg & 1][g] = *reinterpret_cast<const Quad*>(fr + 16 * g);
+            v[rg & 1][QG - 1] = *reinterpret_cast<const Quad*>(fr + last);
         };
-        if (align == 16) {
-            const int4* f4 = reinterpret_cast<const int4*>(fr);
+        load(0);
 #pragma unroll
-            for (int h = 0; h < SQ; h += PK) {
-                int4 v[PK];
+        for (int rg = 0; rg < 4; ++rg) {
+            if (rg + 1 < 4) load(rg + 1);
+            asm volatile("" ::: "memory");
+            uint32_t* d = tile + q0 * SWG + (tid & ~63) + rg * 16 + (lane & 15);
 #pragma unroll
-                for (int q = 0; q < PK; ++q) v[q] = f4[h + q];
-#pragma unroll
-                for (int q = 0; q < PK; ++q) packed[h + q] = pack(v[q].x, v[q].y, v[q].z, v[q].w);
-            }
-        } else if (align == 8) {
-            // an even number of features: the last quad may hold two
-            const int2* f2 = reinterpret_cast<const int2*>(fr);
-            const int n2 = F / 2;
-#pragma unroll
-            for (int h = 0; h < SQ; h += PK) {
-                int2 v[2 * PK];
-#pragma unroll
-                for (int i = 0; i < 2 * PK; ++i) v[i] = f2[2 * h + i < n2 ? 2 * h + i : n2 - 1];
-#pragma unroll
-                for (int q = 0; q < PK; ++q)
-                    packed[h + q] = pack(v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < SQ; ++q) {
-                int x[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = fr[4 * q + i < F ? 4 * q + i : F - 1];
-                packed[q] = pack(x[0], x[1], x[2], x[3]);
+            for (int g = 0; g < QG; ++g) {
+                const Quad& x = v[rg & 1][g];
+                const uint32_t w = byte(x.x) | (byte(x.y) << 8) | (byte(x.z) << 16) | (byte(x.w) << 24);
+                d[4 * g * SWG] = g + 1 < QG ? w : w >> down;
             }
         }
-#pragma unroll
-        for (int q = 0; q < SQ; ++q) tile[q * SWG + tid] = packed[q];
     }
     const uint32_t fb = (uint32_t)S::CW * 4u + (uint32_t)tid * 4u;
     uint16_t* lrow = (LEAVES && row < n) ? leaves + row * e.n_trees : nullptr;
@@ -318,23 +316,16 @@ __global__ __launch_bounds__(SWG) void k_score(EnsembleDesc e, const int32_t* __
     if (row < n) scores[row] = accumulate ? scores[row] + acc : acc;
 }
 
-// Alignment in bytes that every feature row has: 16, 8 or 4.
-int row_align(const EnsembleDesc& e, const int32_t* feats) {
-    const uintptr_t at = reinterpret_cast<uintptr_t>(feats) | ((uintptr_t)e.n_features * 4u);
-    return at % 16u == 0 ? 16 : (at % 8u == 0 ? 8 : 4);
-}
-
 template <int DEPTH, int SQ>
 hipError_t score_q(const EnsembleDesc& e, const int32_t* feats, int64_t n, float* scores, uint16_t* leaves,
                    bool accumulate, hipStream_t stream) {
     const unsigned grid = (unsigned)((n + SWG - 1) / SWG);
-    const int align = row_align(e, feats);
     if (leaves)
         hipLaunchKernelGGL((k_score<DEPTH, true, SQ>), dim3(grid), dim3(SWG), 0, stream, e, feats, n, scores, leaves,
-                           accumulate ? 1 : 0, align);
+                           accumulate ? 1 : 0);
     else
         hipLaunchKernelGGL((k_score<DEPTH, false, SQ>), dim3(grid), dim3(SWG), 0, stream, e, feats, n, scores, leaves,
-                           accumulate ? 1 : 0, align);
+                           accumulate ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -480,17 +471,14 @@ hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream)
 //    x 250 trees: depth 4 159 -> 77 us, depth 8 171 -> 115; depth 8, 500
 //    trees: 32769 rows 103 -> 133, 49153 137 -> 135.  The line rises with the
 //    depth; few trees (depth 8, 20: even from 32769 rows; depth 9, 20: 131072
-//    rows 32 -> 27) cross earlier.  Rows on 4-byte boundaries cost k_score
-//    the more to load (131072 rows x 100 trees of depth 7: 101 -> 71, but
-//    200003 x 20 of depth 5: 82 -> 88).
-bool one_lane_a_row(const EnsembleDesc& e, const int32_t* feats, int64_t n, bool leaves) {
+//    rows 32 -> 27) cross earlier.
+bool one_lane_a_row(const EnsembleDesc& e, int64_t n, bool leaves) {
     const int quads = (e.n_features + 3) / 4, d = e.depth;
     if (quads != 28 && quads != 44 && quads != 48) return false;
     if (!leaves) return n >= 131072 && d <= 8;
     const bool few = (int64_t)e.n_trees * d * d <= 4000;
     const int64_t from = d <= 4 ? 24577 : d <= 6 ? 28673 : d == 7 || (d == 8 && few) ? 36865 : d == 8 ? 49153 : 98305;
     if (d > 9 || (d == 9 && !few)) return false;
-    if (row_align(e, feats) < 8) return !few && n >= 98305;
     return n >= from;
 }
 
@@ -513,7 +501,7 @@ hipError_t launch_score(const EnsembleDesc& e, const int32_t* feats, int64_t n, 
     const bool vec = e.n_features % 4 == 0 && (reinterpret_cast<uintptr_t>(feats) & 15u) == 0;
     RowsPlan pl;
     RowsArgs a{};
-    if (one_lane_a_row(e, feats, n, leaves != nullptr))
+    if (one_lane_a_row(e, n, leaves != nullptr))
         return launch_score_wide(e, feats, n, scores, leaves, accumulate, stream);
     if (!plan_rows(e, n, pl, a)) return hipErrorInvalidConfiguration;
     a.feats = feats;

@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,F,T,depth,offset", [
     (24577, 176, 30, 4, 0), (24576, 176, 30, 4, 0), (28673, 192, 15, 6, 0), (28672, 110, 15, 6, 0), (36865, 110, 9, 7, 0),
-    (36865, 176, 9, 8, 0), (49153, 176, 65, 8, 0), (49152, 192, 65, 8, 0), (98305, 176, 7, 9, 0), (98305, 192, 161, 5, 1),
-    (98304, 110, 161, 5, 1), (98305, 110, 160, 5, 1)])
+    (36865, 176, 9, 8, 0), (49153, 176, 65, 8, 0), (49152, 192, 65, 8, 0), (98305, 176, 7, 9, 0), (28673, 192, 9, 5, 1),
+    (28673, 110, 9, 5, 3)])
 def test_leaves_at_the_lines(P, n, F, T, depth, offset):
     print(f"[gpu-score] leaf lines: n {n} F {F} T {T} depth {depth} offset {offset}", flush=True)
     check(P, W.make_ensemble(T, depth, F, 29), rows_of(n, F, n + F), True, offset)
@@ -46,3 +46,15 @@ def test_leaf_indices_of_many_rows_cost_no_second_walk(P, n, T, depth):
     scores, leaves = call_us(P, tables, n, 176, False), call_us(P, tables, n, 176, True)
     print(f"[gpu-score] n {n} T {T} depth {depth}: {scores:.1f} us, with leaf indices {leaves:.1f} us", flush=True)
     assert leaves < 2.0 * scores
+
+
+@pytest.mark.parametrize("F", [109, 110, 111, 112, 173, 174, 175, 176, 189, 190, 191, 192])
+@pytest.mark.parametrize("n", [131072, 131329])
+def test_rows_that_end_within_their_last_quad(P, F, n):
+    """Every row length of the one-lane-a-row kernel: its last load takes the
+    row's last four features and moves them to their places."""
+    fid, thr, leaf = W.make_ensemble(12, 4, F, 5)
+    fid[:, 0] = F - 1 - np.arange(12) % 5                # every tree looks at the row's end first
+    print(f"[gpu-score] row ends: F {F} n {n}", flush=True)
+    check(P, (fid, thr, leaf), rows_of(n, F, F), False, F % 4)
+    check(P, (fid, thr, leaf), rows_of(n, F, F), True, 0)
