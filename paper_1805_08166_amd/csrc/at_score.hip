@@ -458,28 +458,39 @@ hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream)
     return hipLaunchKernel(fn, dim3((unsigned)((a.n + pl.R - 1) / pl.R)), dim3(pl.waves * 64), args, pl.lds, stream);
 }
 
-// Whether a call that both kernels take goes to k_score.  Measured on rows of
-// 110, 176 and 192 features, k_rows -> k_score:
-//  - Scores: from 131072 rows (two workgroups a compute unit) for trees of up
-//    to eight levels: 2^20 rows of 176 features x 1000 trees of depth 8 take
-//    1.75 ms against 2.3; at 131072 the two are even (148 and 143 us for 500
-//    trees).  Deeper trees leave a lane one or two trees in flight (depth 10,
-//    131072 rows: 307 against 237 us).
+// Whether a call that both kernels take goes to k_score.  The lines come from
+// both kernels' times at 16385 .. 262144 rows of 110, 176 and 192 features,
+// depths 2 .. 9, 20 .. 400 trees (us, k_rows -> k_score, 176 features):
+//  - Scores.  k_rows' time grows with the rows, k_score's with the workgroups
+//    a compute unit has (a step every 65536 rows), and the fewer and
+//    shallower the trees the more of either is the rows' load, which k_score
+//    does in fewer passes.  20 trees of depth 5: 40001 rows 10 -> 8, 131072 26
+//    -> 17; 60 of depth 6: 49153 rows 15 -> 14; 400 of depth 6: 81921 rows 73
+//    -> 77, 98305 79 -> 78; 400 of depth 8: 114689 rows 109 -> 115, 180001
+//    152 -> 147.  Deeper trees leave a lane one or two trees in flight (depth
+//    10, 131072 rows: 237 -> 307).
 //  - With leaf indices: k_rows' lanes store eight bytes of a row at a time,
 //    all over the rows of a workgroup, which costs more than the walk from 64
-//    rows a workgroup on; a k_score lane goes along its own row.  131072 rows
-//    x 250 trees: depth 4 159 -> 77 us, depth 8 171 -> 115; depth 8, 500
-//    trees: 32769 rows 103 -> 133, 49153 137 -> 135.  The line rises with the
-//    depth; few trees (depth 8, 20: even from 32769 rows; depth 9, 20: 131072
-//    rows 32 -> 27) cross earlier.
+//    rows a workgroup (24577 rows) on; a k_score lane goes along its own row.
+//    131072 rows x 100 trees of depth 4 75 -> 34, x 250 of depth 8 171 ->
+//    114; 150 of depth 8: 32769 rows 35 -> 41, 49153 47 -> 44; 150 of depth 9:
+//    131072 rows 120 -> 94, 180001 160 -> 169.
 bool one_lane_a_row(const EnsembleDesc& e, int64_t n, bool leaves) {
     const int quads = (e.n_features + 3) / 4, d = e.depth;
-    if (quads != 28 && quads != 44 && quads != 48) return false;
-    if (!leaves) return n >= 131072 && d <= 8;
-    const bool few = (int64_t)e.n_trees * d * d <= 4000;
-    const int64_t from = d <= 4 ? 24577 : d <= 6 ? 28673 : d == 7 || (d == 8 && few) ? 36865 : d == 8 ? 49153 : 98305;
-    if (d > 9 || (d == 9 && !few)) return false;
-    return n >= from;
+    if ((quads != 28 && quads != 44 && quads != 48) || d > 9) return false;
+    const int64_t work = (int64_t)e.n_trees * d * d;
+    if (leaves) {
+        if (d <= 6) return n >= 24577;
+        if (d == 7 || (d == 8 && work <= 4000)) return n >= 32769;
+        if (d == 8) return n >= 45057;
+        return work <= 2000 ? n >= 65537 : n >= 81921 && n <= 131072;
+    }
+    if (d == 9) return work <= 4000 && n >= (work <= 2000 ? 65537 : 98305);
+    if (work <= 1600) return n >= 32769;
+    if (work <= 4000 && d <= 7) return n >= 49153;
+    if (d <= 6 || work <= 4000 || (d == 7 && work <= 8000)) return n >= 98305;
+    if (d == 7 || work <= 10000) return n >= 114689;
+    return n >= 131072;
 }
 
 }  // namespace

@@ -10,13 +10,21 @@ from test_gpu_score import DEV, P, check, rows_of  # noqa: F401  (P: the fixture
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,F,T,depth,offset", [
-    (24577, 176, 30, 4, 0), (24576, 176, 30, 4, 0), (28673, 192, 15, 6, 0), (28672, 110, 15, 6, 0), (36865, 110, 9, 7, 0),
-    (36865, 176, 9, 8, 0), (49153, 176, 65, 8, 0), (49152, 192, 65, 8, 0), (98305, 176, 7, 9, 0), (28673, 192, 9, 5, 1),
-    (28673, 110, 9, 5, 3)])
-def test_leaves_at_the_lines(P, n, F, T, depth, offset):
-    print(f"[gpu-score] leaf lines: n {n} F {F} T {T} depth {depth} offset {offset}", flush=True)
-    check(P, W.make_ensemble(T, depth, F, 29), rows_of(n, F, n + F), True, offset)
+@pytest.mark.parametrize("n,F,T,depth,offset,leaves", [
+    # with leaf indices: either side of each line
+    (24577, 176, 30, 4, 0, True), (24576, 176, 30, 4, 0, True), (24577, 192, 15, 6, 1, True),
+    (32769, 110, 9, 7, 0, True), (32768, 110, 9, 7, 3, True), (32769, 176, 9, 8, 0, True),
+    (45057, 176, 65, 8, 0, True), (45056, 192, 65, 8, 0, True), (65537, 176, 24, 9, 0, True),
+    (81921, 192, 25, 9, 0, True), (131072, 176, 25, 9, 0, True), (131073, 176, 25, 9, 0, True),
+    # scores alone
+    (32769, 176, 25, 8, 0, False), (32768, 176, 25, 8, 0, False), (32769, 110, 1600, 1, 2, False),
+    (49153, 192, 80, 7, 0, False), (49152, 176, 80, 7, 1, False), (65537, 176, 24, 9, 0, False),
+    (98305, 176, 112, 6, 0, False), (98304, 192, 112, 6, 0, False), (98305, 110, 60, 8, 0, False),
+    (98305, 176, 49, 9, 0, False), (114689, 176, 170, 7, 0, False), (114688, 192, 156, 8, 0, False),
+    (114689, 192, 156, 8, 0, False), (131072, 176, 157, 8, 0, False), (131071, 110, 157, 8, 1, False)])
+def test_scores_at_the_lines(P, n, F, T, depth, offset, leaves):
+    print(f"[gpu-score] lines: n {n} F {F} T {T} depth {depth} offset {offset} leaves {leaves}", flush=True)
+    check(P, W.make_ensemble(T, depth, F, 29), rows_of(n, F, n + F), leaves, offset)
 
 
 def call_us(P, tables, n, F, leaves):
@@ -58,3 +66,13 @@ def test_rows_that_end_within_their_last_quad(P, F, n):
     print(f"[gpu-score] row ends: F {F} n {n}", flush=True)
     check(P, (fid, thr, leaf), rows_of(n, F, F), False, F % 4)
     check(P, (fid, thr, leaf), rows_of(n, F, F), True, 0)
+
+
+@pytest.mark.parametrize("T,depth", [(40, 3), (100, 4)])
+def test_one_row_fewer_costs_no_more(P, T, depth):
+    """131071 rows against 131072, where one row decided the kernel: 26 us
+    against 21 for 40 trees of depth 3."""
+    tables = W.make_ensemble(T, depth, 176, 5)
+    below, at = call_us(P, tables, 131071, 176, False), call_us(P, tables, 131072, 176, False)
+    print(f"[gpu-score] T {T} depth {depth}: 131071 rows {below:.1f} us, 131072 {at:.1f}", flush=True)
+    assert below < 1.1 * at
