@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -277,6 +278,12 @@ at_status hip_fail(hipError_t e, const char* what);
 // Space construction (at_space.cpp).
 at_status build_space(int tmpl, const int64_t* shape, int nshape, SpaceDesc& desc,
                       std::vector<uint64_t>& factors);
+
+// Before a kernel's launches on the current device, once per kernel and
+// device (a bit of `done` each): checks that its static LDS takes static_lds
+// bytes (unless negative) and lets a launch ask for dynamic_lds bytes of
+// dynamic LDS (unless 0).  Any number of threads may call it at once.
+hipError_t prepare_kernel(const void* fn, int64_t static_lds, size_t dynamic_lds, std::atomic<uint64_t>& done);
 
 // Kernel launchers (at_kernels.hip).
 hipError_t launch_extract(const at_space_s& sp, const uint64_t* cfgs, int64_t n, int32_t* feats,

@@ -448,8 +448,9 @@ hipError_t predict_depth(const EnsembleDesc& e, const int32_t* feats, int64_t n,
     const int Q = (e.n_features + 3) / 4;
     const int ct = chunk_trees_for(DEPTH, CHUNK_BYTES);
     const size_t lds = (size_t)Q * WG * 4 + (size_t)ct * (2 << DEPTH) * 4;
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_predict<DEPTH>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    static std::atomic<uint64_t> done;
+    const hipError_t err = prepare_kernel(reinterpret_cast<const void*>(&k_predict<DEPTH>), -1,
+                                          MAX_TILE_QUADS * WG * 4 + CHUNK_BYTES, done);
     if (err != hipSuccess) return err;
     const unsigned grid = (unsigned)((n + WG - 1) / WG);
     hipLaunchKernelGGL((k_predict<DEPTH>), dim3(grid), dim3(WG), lds, stream, e, feats, n, scores, leaves, ct,

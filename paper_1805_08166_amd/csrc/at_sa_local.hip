@@ -579,24 +579,14 @@ hipError_t launch_local_t(const LocalArgs& a, int depth, int grid, int threads, 
 #undef AT_LOCAL_CASE
         default: return hipErrorInvalidValue;
     }
-    static bool configured[13] = {};
-    if (!configured[depth]) {
-        // the walk addresses the tile with an and-or, which needs the
-        // dynamic LDS block at address 0: no static LDS in the kernel
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, fn);
-        if (e != hipSuccess) return e;
-        if (fa.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LOCAL_LDS_BYTES);
-        if (e != hipSuccess) return e;
-        configured[depth] = true;
-    }
+    // the walk addresses the tile with an and-or, which needs the dynamic LDS
+    // block at address 0: no static LDS in the kernel
+    static std::atomic<uint64_t> done[13];
+    hipError_t e = prepare_kernel(fn, 0, LOCAL_LDS_BYTES, done[depth]);
+    if (e != hipSuccess) return e;
     void* args[] = {const_cast<LocalArgs*>(&a)};
-    if (start) {
-        hipError_t e = hipEventRecord(start, stream);
-        if (e != hipSuccess) return e;
-    }
-    hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, stream);
+    if (start && (e = hipEventRecord(start, stream)) != hipSuccess) return e;
+    e = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, stream);
     if (e != hipSuccess) return e;
     if (stop) return hipEventRecord(stop, stream);
     return hipSuccess;

@@ -25,7 +25,6 @@
 // wave 0, took 3.76 us a step on the C2 search (1024 chains, 500 trees of
 // depth 8) and 2.50 on the GEMM one (64 chains, 100 trees of depth 6); this
 // one 3.3 and 1.26.
-#include <atomic>
 #include <type_traits>
 
 #include "at_chain.h"
@@ -557,17 +556,10 @@ __global__ __launch_bounds__(NT) void k_single(SingleArgs a) {
 
 template <int TMPL, int DEPTH, bool TAIL, int NT>
 hipError_t launch_single_nt(const SingleArgs& a, const LocalPlan& pl, hipStream_t stream) {
-    static std::atomic<uint64_t> configured;   // the devices this is done on, a bit each
+    static std::atomic<uint64_t> done;
     const void* fn = reinterpret_cast<const void*>(&k_single<TMPL, DEPTH, TAIL, NT>);
-    int device = 0;
-    hipError_t e = hipGetDevice(&device);
+    const hipError_t e = prepare_kernel(fn, -1, SINGLE_LDS_BYTES, done);
     if (e != hipSuccess) return e;
-    const uint64_t bit = device < 64 ? (uint64_t)1 << device : 0;
-    if (!(configured.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SINGLE_LDS_BYTES);
-        if (e != hipSuccess) return e;
-        configured.fetch_or(bit, std::memory_order_release);
-    }
     void* args[] = {const_cast<SingleArgs*>(&a)};
     return hipLaunchKernel(fn, dim3(pl.grid), dim3(NT), args, pl.lds_bytes, stream);
 }

@@ -1410,16 +1410,12 @@ bool plan_trees(int depth, int Q, uint32_t slot, int nw, int tpw, bool in_slot, 
 template <int DEPTH, int QT, bool ONE>
 hipError_t launch_trees_t(const TreeArgs& a, int nw, hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
     const int grid = (a.n_trees + a.tpw - 1) / a.tpw * a.slices;
-    static bool checked = false;
-    if (!checked) {
-        // the walk's asm takes offsets into the kernel's LDS array as LDS
-        // addresses: the array must be the kernel's only LDS object
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&k_trees<DEPTH, QT, ONE>));
-        if (e != hipSuccess) return e;
-        if (fa.sharedSizeBytes != MAX_LDS_BYTES) return hipErrorInvalidKernelFile;
-        checked = true;
-    }
+    // the walk's asm takes offsets into the kernel's LDS array as LDS
+    // addresses: the array must be the kernel's only LDS object
+    static std::atomic<uint64_t> done;
+    const hipError_t e =
+        prepare_kernel(reinterpret_cast<const void*>(&k_trees<DEPTH, QT, ONE>), MAX_LDS_BYTES, 0, done);
+    if (e != hipSuccess) return e;
     if (start)
         hipExtLaunchKernelGGL((k_trees<DEPTH, QT, ONE>), dim3(grid), dim3(nw * 64), 0, stream, start, stop, 0, a);
     else
@@ -1663,23 +1659,18 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
                                  (int64_t)ta.q, (int64_t)groups * n16 * 16};
         for (int i = 0; i < 8; ++i) ch.last_plan[i] = plan[i];
     }
-    static bool chain_configured = false;
-    if (!chain_configured) {
-        for (const void* f : {reinterpret_cast<const void*>(&k_chain<AT_TMPL_GEMM>),
-                              reinterpret_cast<const void*>(&k_chain<AT_TMPL_CONV2D_NCHW>)}) {
-            if ((err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)(ring_bytes(true) + (size_t)CPW * KMAX * sizeof(at_entry)))) != hipSuccess)
-                return err;
-        }
-        chain_configured = true;
-    }
+    static std::atomic<uint64_t> chain_done[2];
+    const bool gemm = sp.tmpl == AT_TMPL_GEMM;
+    auto kern = gemm ? k_chain<AT_TMPL_GEMM> : k_chain<AT_TMPL_CONV2D_NCHW>;
+    if ((err = prepare_kernel(reinterpret_cast<const void*>(kern), -1,
+                              ring_bytes(true) + (size_t)CPW * KMAX * sizeof(at_entry), chain_done[gemm])) != hipSuccess)
+        return err;
     ch.events_used[0] = ch.events_used[1] = 0;
     auto chain_kernel = [&](const ChainArgs& x) -> hipError_t {
         const size_t lds = x.fin == FIN_NONE ? 0 : chain_lds;
         hipEvent_t start, stop;
         const hipError_t ev = next_events(ch, 1, start, stop);
         if (ev != hipSuccess) return ev;
-        auto kern = sp.tmpl == AT_TMPL_GEMM ? k_chain<AT_TMPL_GEMM> : k_chain<AT_TMPL_CONV2D_NCHW>;
         if (start)
             hipExtLaunchKernelGGL(kern, dim3(chain_grid), dim3(CHAIN_WG), lds, stream, start, stop, 0, x);
         else

@@ -7,7 +7,6 @@
 //            thresholds above six bits, of 28, 44 or 48 feature quads (GEMM
 //            and conv2d loop-context rows, relation rows)
 #include <algorithm>
-#include <atomic>
 
 #include "at_chain.h"
 
@@ -364,27 +363,8 @@ hipError_t launch_score_wide(const EnsembleDesc& e, const int32_t* feats, int64_
 
 namespace {
 
-// Dynamic LDS a scoring workgroup may use: the compute unit's 160 KB less 1
-// KB kept for any static LDS the compiler places.
+// Dynamic LDS a scoring workgroup may use: the compute unit's 160 KB less 1 KB.
 constexpr size_t SCORE_LDS_BYTES = 163840 - 1024;
-
-// The walks address the tile with an and-or, which needs the dynamic LDS
-// block at address 0: no static LDS in the kernel.  Raises the kernel's
-// dynamic LDS limit, once per kernel and device (a bit of `done` each).
-hipError_t configure(const void* fn, std::atomic<uint64_t>& done) {
-    int device = 0;
-    hipError_t e = hipGetDevice(&device);
-    if (e != hipSuccess) return e;
-    const uint64_t bit = device < 64 ? (uint64_t)1 << device : 0;
-    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
-    hipFuncAttributes fa;
-    e = hipFuncGetAttributes(&fa, fn);
-    if (e != hipSuccess) return e;
-    if (fa.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCORE_LDS_BYTES);
-    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
-    return e;
-}
 
 struct RowsPlan {
     bool tail = false;
@@ -452,7 +432,9 @@ hipError_t rows_depth(const RowsPlan& pl, const RowsArgs& a, hipStream_t stream)
     const bool tail = TAILS && pl.tail;
     const void* fn = tail ? reinterpret_cast<const void*>(&k_rows<DEPTH, TAILS>)
                           : reinterpret_cast<const void*>(&k_rows<DEPTH, false>);
-    hipError_t e = configure(fn, done[tail]);
+    // the walks address the tile with an and-or, which needs the dynamic LDS
+    // block at address 0: no static LDS in the kernel
+    hipError_t e = prepare_kernel(fn, 0, SCORE_LDS_BYTES, done[tail]);
     if (e != hipSuccess) return e;
     void* args[] = {const_cast<RowsArgs*>(&a)};
     return hipLaunchKernel(fn, dim3((unsigned)((a.n + pl.R - 1) / pl.R)), dim3(pl.waves * 64), args, pl.lds, stream);

@@ -846,14 +846,9 @@ struct SelectCache {
 hipError_t launch_select(const at_space_s& sp, const at_entry* cand, int64_t n_cand, int pool, int n_greedy,
                          float alpha, int n_random, uint64_t seed, at_entry* out, hipStream_t stream,
                          at_entry* scratch) {
-    static bool configured = false;
-    hipError_t e = hipSuccess;
-    if (!configured) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_select), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)select_lds_bytes());
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static std::atomic<uint64_t> done;
+    hipError_t e = prepare_kernel(reinterpret_cast<const void*>(&k_select), -1, select_lds_bytes(), done);
+    if (e != hipSuccess) return e;
     // reduce the candidates to at most FINAL_MAX entries: each level keeps
     // the `keep` best distinct of every CHUNK-entry slice as a run of `slots`
     // (half a slice or less)
