@@ -68,9 +68,7 @@ struct LocalArgs {
     int n_chunks;
     int resident;             // the ring holds every tree (loaded once); else two chunk buffers
     int walk_waves;           // waves 1 .. walk_waves walk; later waves load
-    int tail;                 // tree tops resident, last level and leaves from the tail records
     const uint4* tail_rec;    // [T][2^(d-1)] records {node, left leaf, right leaf, 0}
-    int gather;               // tree tops streamed, last level and leaves from the tail records
     // dynamic LDS layout (byte offsets; the feature tile is at 0)
     uint32_t off_ring, ring_bytes;
     uint32_t off_lv;
@@ -93,7 +91,16 @@ __device__ __forceinline__ void load_trees(const LocalArgs& a, uint8_t* dst, int
 }
 
 
-template <int TMPL, int DEPTH>
+// SINGLE: every tree is walked in one pass a round (whole trees in one chunk,
+// or tree tops, all resident); such runs work a round ahead.  Else the trees
+// pass in chunks, streamed or resident.  TOPS: tree tops, the last level and
+// its leaves from the tail records; else whole trees.  The four are compiled
+// apart: in one kernel the walks of every form and the records in flight of
+// the gathered one shared 255 vector registers, with some 170 scalar ones
+// spilled (200 and 110 apart).  512^3 GEMM, us a step, one kernel -> four:
+// 4096 chains x 2000 trees of depth 4 46.5 -> 41.0, x 250 of depth 9 12.8 ->
+// 10.9, 8192 x 250 of depth 9 21.1 -> 18.1, 2048 x 100 of depth 6 3.68 -> 3.25.
+template <int TMPL, int DEPTH, bool SINGLE, bool TOPS>
 __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
     using N = Nest<TMPL>;
     constexpr int Q = (N::F + 3) / 4;
@@ -193,10 +200,10 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
     }
     if (tid < 2) s_any[tid] = 0u;
     const int rounds = (a.init ? 1 : 0) + a.steps;
-    const bool resident = a.resident != 0 || a.tail != 0;
+    const bool resident = SINGLE || (!TOPS && a.resident != 0);
     const int nck = a.n_chunks;
     const int total_chunks = rounds * nck;
-    const int lag = a.gather ? 2 : 1;   // chunks between a walk and the fold of its leaf values
+    constexpr int lag = TOPS ? 2 : 1;   // chunks between a walk and the fold of its leaf values
     // the first chunk (every tree when resident) is loaded by all waves but 0
     if (wave >= 1 && rounds > 0) {
         load_trees(a, ring, 0, resident ? a.T : (a.ct < a.T ? a.ct : a.T), tid - 64, nthreads - 64);
@@ -229,9 +236,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
         });
     if (owner && a.steps > 0)
         with_space([&](const SpaceDesc& sd) { draw_move(sd, k0, k1, gchain, a.step0, mv_j, mv_v, mv_radix); });
-    // single pass: every tree walked in one pass per round (tail mode, or
-    // resident trees in one chunk); such runs work a round ahead
-    const bool single = a.tail || (a.resident && a.n_chunks == 1);
+    constexpr bool single = SINGLE;
 
     // Loop gr's features of chain j's configuration nx into row dst.
     auto eval_loop = [&](const uint32_t (&nx)[MAX_KNOBS], int j, int gr_, uint8_t* dst) {
@@ -329,7 +334,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
             }
         }
         float sc = 0.0f;
-        if (single) {
+        if constexpr (SINGLE) {
             // (4') every tree of every chain in one pass: in tail mode the
             // resident top levels from LDS, then the last level and its leaf
             // from the tree's 16-byte tail record; else the whole tree from
@@ -359,7 +364,7 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
             // (tail mode keeps every slot busy: its last-level gathers, not
             // the walks, set the pace)
             const int want = (a.T + 3) >> 2, have = nthreads / cpb;
-            const int S = (a.tail || want > have) ? have : want;
+            const int S = (TOPS || want > have) ? have : want;
             const int ua = tid / cpb;
             const int ja = tid & (cpb - 1);
             const uint32_t fba = lbase | (uint32_t)lane * 4u;
@@ -371,12 +376,12 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
                     nb[g] = lbase + a.off_ring + (uint32_t)(t < a.T ? t : 0) * (uint32_t)a.ts * 4u;
                 }
             };
-            if (a.tail) {
+            if constexpr (TOPS) {
                 for (int base = 0; base < a.T; base += 4 * S) {
                     uint32_t nb[4], q[4];
                     int ti[4];
                     trees_of(base, ti, nb);
-                    walk4_local<(DEPTH >= 2 ? DEPTH - 1 : 1)>(nb, fba, q);
+                    walk4_local<DEPTH - 1>(nb, fba, q);
                     uint4 rec4[4];
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
@@ -458,10 +463,9 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
                         ti[g] = tl < nt ? tl : -1;
                         nb[g] = rb + (uint32_t)(tl < nt ? tl : u) * (uint32_t)a.ts * 4u;
                     }
-                    if (a.gather) walk4_local<(DEPTH >= 2 ? DEPTH - 1 : 1)>(nb, fb, q);
-                    else walk4_local<DEPTH>(nb, fb, q);
+                    walk4_local<(TOPS ? DEPTH - 1 : DEPTH)>(nb, fb, q);
                 }
-                if (a.gather) {
+                if constexpr (TOPS) {
                     // the last levels from the records gathered last
                     // iteration, then this chunk's records
                     if (it > 0 && jw < nc) {
@@ -567,22 +571,14 @@ __global__ __launch_bounds__(LOCAL_WG_MAX) void k_local(LocalArgs a) {
     }
 }
 
-template <int TMPL>
-hipError_t launch_local_t(const LocalArgs& a, int depth, int grid, int threads, size_t lds, hipStream_t stream,
-                          hipEvent_t start, hipEvent_t stop) {
-    const void* fn = nullptr;
-    switch (depth) {
-#define AT_LOCAL_CASE(D) \
-    case D: fn = reinterpret_cast<const void*>(&k_local<TMPL, D>); break;
-        AT_LOCAL_CASE(1) AT_LOCAL_CASE(2) AT_LOCAL_CASE(3) AT_LOCAL_CASE(4) AT_LOCAL_CASE(5) AT_LOCAL_CASE(6)
-        AT_LOCAL_CASE(7) AT_LOCAL_CASE(8) AT_LOCAL_CASE(9) AT_LOCAL_CASE(10) AT_LOCAL_CASE(11) AT_LOCAL_CASE(12)
-#undef AT_LOCAL_CASE
-        default: return hipErrorInvalidValue;
-    }
+template <int TMPL, int DEPTH, bool SINGLE, bool TOPS>
+hipError_t launch_local_f(const LocalArgs& a, int grid, int threads, size_t lds, hipStream_t stream, hipEvent_t start,
+                          hipEvent_t stop) {
     // the walk addresses the tile with an and-or, which needs the dynamic LDS
     // block at address 0: no static LDS in the kernel
-    static std::atomic<uint64_t> done[13];
-    hipError_t e = prepare_kernel(fn, 0, LOCAL_LDS_BYTES, done[depth]);
+    static std::atomic<uint64_t> done;
+    const void* fn = reinterpret_cast<const void*>(&k_local<TMPL, DEPTH, SINGLE, TOPS>);
+    hipError_t e = prepare_kernel(fn, 0, LOCAL_LDS_BYTES, done);
     if (e != hipSuccess) return e;
     void* args[] = {const_cast<LocalArgs*>(&a)};
     if (start && (e = hipEventRecord(start, stream)) != hipSuccess) return e;
@@ -590,6 +586,32 @@ hipError_t launch_local_t(const LocalArgs& a, int depth, int grid, int threads, 
     if (e != hipSuccess) return e;
     if (stop) return hipEventRecord(stop, stream);
     return hipSuccess;
+}
+
+template <int TMPL, int DEPTH>
+hipError_t launch_local_d(const LocalArgs& a, const LocalPlan& pl, hipStream_t stream, hipEvent_t start,
+                          hipEvent_t stop) {
+    const int g = pl.grid, t = pl.threads;
+    const size_t l = pl.lds_bytes;
+    if constexpr (DEPTH >= 2) {
+        if (pl.tail) return launch_local_f<TMPL, DEPTH, true, true>(a, g, t, l, stream, start, stop);
+        if (pl.gather) return launch_local_f<TMPL, DEPTH, false, true>(a, g, t, l, stream, start, stop);
+    }
+    return pl.resident && pl.n_chunks == 1 ? launch_local_f<TMPL, DEPTH, true, false>(a, g, t, l, stream, start, stop)
+                                           : launch_local_f<TMPL, DEPTH, false, false>(a, g, t, l, stream, start, stop);
+}
+
+template <int TMPL>
+hipError_t launch_local_t(const LocalArgs& a, const LocalPlan& pl, int depth, hipStream_t stream, hipEvent_t start,
+                          hipEvent_t stop) {
+    switch (depth) {
+#define AT_LOCAL_CASE(D) \
+    case D: return launch_local_d<TMPL, D>(a, pl, stream, start, stop);
+        AT_LOCAL_CASE(1) AT_LOCAL_CASE(2) AT_LOCAL_CASE(3) AT_LOCAL_CASE(4) AT_LOCAL_CASE(5) AT_LOCAL_CASE(6)
+        AT_LOCAL_CASE(7) AT_LOCAL_CASE(8) AT_LOCAL_CASE(9) AT_LOCAL_CASE(10) AT_LOCAL_CASE(11) AT_LOCAL_CASE(12)
+#undef AT_LOCAL_CASE
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -760,9 +782,7 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     a.ct = pl.ct;
     a.n_chunks = pl.n_chunks;
     a.resident = pl.resident;
-    a.tail = pl.tail;
     a.tail_rec = e.tail;
-    a.gather = pl.gather;
     a.off_ring = pl.off_ring;
     a.ring_bytes = pl.ring_bytes;
     a.off_lv = pl.off_lv;
@@ -778,8 +798,8 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     hipEvent_t start = nullptr, stop = nullptr;
     if ((err = next_events(ch, 0, start, stop)) != hipSuccess) return err;
     if (sp.tmpl == AT_TMPL_GEMM)
-        return launch_local_t<AT_TMPL_GEMM>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream, start, stop);
-    return launch_local_t<AT_TMPL_CONV2D_NCHW>(a, e.depth, pl.grid, pl.threads, pl.lds_bytes, stream, start, stop);
+        return launch_local_t<AT_TMPL_GEMM>(a, pl, e.depth, stream, start, stop);
+    return launch_local_t<AT_TMPL_CONV2D_NCHW>(a, pl, e.depth, stream, start, stop);
 }
 
 }  // namespace at
