@@ -154,6 +154,7 @@ at_status build_stage(at_space_s& sp) {
     if (st != AT_OK) return st;
     if (sp.n_spaces == 1) {
         sp.stage_single = fits[0] ? 0 : -1;
+        sp.stage_part = !fits[0];
         return AT_OK;
     }
     const int64_t n = sp.chain_offsets.back();
@@ -166,6 +167,7 @@ at_status build_stage(at_space_s& sp) {
         int wh = w;
         while (wh + 1 < sp.n_spaces && sp.chain_offsets[wh + 1] <= hi) ++wh;
         ws[(size_t)b] = (wh == w && fits[w]) ? w : -1;
+        sp.stage_part |= ws[(size_t)b] < 0;
     }
     return upload(sp.d_wg_space, ws.data(), ws.size());
 }

@@ -206,6 +206,7 @@ struct at_space_s {
     at::DeviceBuf d_stage;
     int stage_stride = 0;
     int stage_single = -1;
+    bool stage_part = false;                // some block of chains has no image
     at::DeviceBuf d_wg_space;
     // per member space: its suffix products as host data (for building sets)
     std::vector<std::vector<uint64_t>> host_suffix;

@@ -38,11 +38,9 @@ __device__ __forceinline__ int64_t v_index(int64_t c, int t, int groups) {
     return ((((c >> 4) * groups + (t >> 2)) << 6) + ((c & 15) << 2) + (t & 3));
 }
 
-// Chain-kernel workgroups: wave 0 folds, the others build the next
-// candidates.  (Eight waves measured no faster on either side of the fold's
-// length: twelve conv2d workloads, 1000 trees, 9.8 us a launch against 9.6;
-// C12, 2000 trees, 15.6 against 15.0.)
-constexpr int CHAIN_WG = 256;
+// Chain-kernel workgroups have 256 or 512 threads (template argument
+// CHAIN_WG): wave 0 folds, the others build the next candidates (see
+// launch_sa_tp for the choice).
 constexpr int CPW = 16;                 // chains per chain-kernel workgroup
 static_assert(CPW == 16 && CPW == STAGE_CHAINS, "a chain-kernel workgroup reads one 16-chain block of V");
 constexpr int FOLD_P = 32;              // 4-tree groups per fold pass: 32 x 16 chains x 16 B = 8 KB
@@ -507,7 +505,7 @@ struct TpRec {
 // once the score is known the owner lanes (wave 0, lane j: chain c0 + j)
 // offer the candidate to the best list, take the Metropolis decision and
 // the rows of the candidate that follows go out.
-template <int TMPL>
+template <int TMPL, int CHAIN_WG>
 __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     using N = Nest<TMPL>;
     constexpr int L = N::L;
@@ -570,16 +568,20 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
     int64_t thr_i = a.fin == FIN_STEP ? c * a.steps + a.fin_step : c;
     asm volatile("" : "+v"(thr_i));   // one load from either table (not two loads and a join)
     const float thr_v = thr_b[thr_i];
-    // features at the tile positions of quad `lane` (the last quad's for the
-    // lanes past it, so that every lane loads)
+    // compact tiles (32 quads at most): features at the tile positions of
+    // quad lane % 32 (the last quad's for the lanes past it, so that every
+    // lane loads); taken apart where it is used, so that the folding wave
+    // does not wait for it
+    const int fquad = lane & 31;
     const uint32_t src4 =
-        a.fident ? 0u : *reinterpret_cast<const uint32_t*>(a.fsrc + 4 * (lane < a.fq ? lane : a.fq - 1));
+        a.fident ? 0u : *reinterpret_cast<const uint32_t*>(a.fsrc + 4 * (fquad < a.fq ? fquad : a.fq - 1));
 
     // Rows first, first + stride, ... (count of them; row 2j + o is chain j's
     // candidate after outcome o) from their features to tile words, by one
-    // wave.  Compact tiles: lane q packs quad q (4x+3 per byte, padding 0; a
-    // feature value x <= 63 makes (x << 2) | 3 stay within its byte); tiles of
-    // every feature in order are read from the rows themselves.  Eq. 4 runs:
+    // wave.  Compact tiles: a lane packs one quad of every other row (4x+3 per
+    // byte, padding 0; a feature value x <= 63 makes (x << 2) | 3 stay within
+    // its byte); tiles of every feature in order are read from the rows
+    // themselves.  Eq. 4 runs:
     // lanes take (row, buffer) pairs for the context relation features
     // (Section 4), laid out [pair][buffer][t - 1].  Made here, beside the
     // fold, rather than after the decision: Eq. 4's chain kernel went from
@@ -588,18 +590,20 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
         __builtin_amdgcn_s_waitcnt(0xc07f);      // this wave's own rows are in LDS
         __builtin_amdgcn_wave_barrier();
         if (!a.fident) {
-#pragma unroll 4
-            for (int i = 0; i < count; ++i) {
+            uint32_t foff[4], fpad = 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t f = (src4 >> (8 * i)) & 0xffu;
+                foff[i] = f == 0xffu ? 0u : f;
+                fpad |= f == 0xffu ? 0xffu << (8 * i) : 0u;
+            }
+#pragma unroll 3
+            for (int i = lane >> 5; i < count; i += 2) {
                 const int jo = first + i * stride, j = jo >> 1, o = jo & 1;
                 const uint8_t* row = frow[o][j];
-                uint32_t w = 0u;
-#pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const uint32_t f = (src4 >> (8 * i4)) & 0xffu;
-                    const uint32_t x = row[f < (uint32_t)N::F ? f : 0u];
-                    if (f != 0xffu) w |= ((x << 2) | 3u) << (8 * i4);
-                }
-                if (lane < a.fq) s_tile[o][j][lane] = w;
+                const uint32_t w = (uint32_t)row[foff[0]] | ((uint32_t)row[foff[1]] << 8) |
+                                   ((uint32_t)row[foff[2]] << 16) | ((uint32_t)row[foff[3]] << 24);
+                if (fquad < a.fq) s_tile[o][j][fquad] = ((w << 2) | 0x03030303u) & ~fpad;
             }
         }
         if (a.Fr) {
@@ -824,8 +828,8 @@ __global__ __launch_bounds__(CHAIN_WG) void k_chain(ChainArgs a) {
         // memory as well.  Skipped when no chain qualifies.
         if (s_any) {
             const int64_t cg = c0 + (gvalid ? gj : 0);
-            group_offer(lists + gj * k, rec[gj], k, gr, gmask, gvalid && rec[gj].qual != 0, a.top + cg * k,
-                        a.meta + cg);
+            TpRec& R = rec[gvalid ? gj : 0];
+            group_offer(lists + gj * k, R, k, gr, gmask, gvalid && R.qual != 0, a.top + cg * k, a.meta + cg);
         }
         if (a.best) {
             lds_barrier();
@@ -1632,6 +1636,7 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
     ca.fsrc = static_cast<const uint8_t*>(sp.d_fsrc.p);
     ca.fq = sp.tile_q;
     ca.fident = sp.tile_q == Q ? 1 : 0;
+    if (!ca.fident && ca.fq > 32) return hipErrorInvalidValue;   // the chain kernel packs compact tiles by half waves
     if (eg) {
         ca.Vg = static_cast<const float*>(ch.d_vg.p);
         ca.Tg = eg->n_trees;
@@ -1659,11 +1664,23 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
                                  (int64_t)ta.q, (int64_t)groups * n16 * 16};
         for (int i = 0; i < 8; ++i) ch.last_plan[i] = plan[i];
     }
-    static std::atomic<uint64_t> chain_done[2];
+    // While wave 0 folds, the other waves build and finish both next
+    // candidates of 16 chains.  Three of them do it within a fold of some 700
+    // trees; shorter folds, and chains whose space tables come from global
+    // memory (a block over two spaces of a set), take seven, as long as a
+    // compute unit has one workgroup (us a step, 256 -> 512 threads: C2, 1024
+    // chains, 300 trees 13.5 -> 13.0, 900 trees 15.3 -> 15.5, 20000 chains,
+    // 300 trees 35.4 -> 37.8; twelve spaces x 100 chains, 1000 trees 23.5 ->
+    // 22.1; Eq. 4, 12 x 16 chains 19.9 -> 20.6).
+    const bool wide = chain_grid <= (unsigned)n_cu && ((!eg && e.n_trees <= 700) || sp.stage_part);
+    static std::atomic<uint64_t> chain_done[2][2];
     const bool gemm = sp.tmpl == AT_TMPL_GEMM;
-    auto kern = gemm ? k_chain<AT_TMPL_GEMM> : k_chain<AT_TMPL_CONV2D_NCHW>;
+    auto kern = gemm ? (wide ? k_chain<AT_TMPL_GEMM, 512> : k_chain<AT_TMPL_GEMM, 256>)
+                     : (wide ? k_chain<AT_TMPL_CONV2D_NCHW, 512> : k_chain<AT_TMPL_CONV2D_NCHW, 256>);
+    const dim3 chain_wg(wide ? 512 : 256);
     if ((err = prepare_kernel(reinterpret_cast<const void*>(kern), -1,
-                              ring_bytes(true) + (size_t)CPW * KMAX * sizeof(at_entry), chain_done[gemm])) != hipSuccess)
+                              ring_bytes(true) + (size_t)CPW * KMAX * sizeof(at_entry), chain_done[gemm][wide])) !=
+        hipSuccess)
         return err;
     ch.events_used[0] = ch.events_used[1] = 0;
     auto chain_kernel = [&](const ChainArgs& x) -> hipError_t {
@@ -1672,9 +1689,9 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
         const hipError_t ev = next_events(ch, 1, start, stop);
         if (ev != hipSuccess) return ev;
         if (start)
-            hipExtLaunchKernelGGL(kern, dim3(chain_grid), dim3(CHAIN_WG), lds, stream, start, stop, 0, x);
+            hipExtLaunchKernelGGL(kern, dim3(chain_grid), chain_wg, lds, stream, start, stop, 0, x);
         else
-            hipLaunchKernelGGL(kern, dim3(chain_grid), dim3(CHAIN_WG), lds, stream, x);
+            hipLaunchKernelGGL(kern, dim3(chain_grid), chain_wg, lds, stream, x);
         return hipGetLastError();
     };
     auto trees_kernel = [&]() -> hipError_t {
