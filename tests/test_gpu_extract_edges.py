@@ -49,3 +49,25 @@ def test_rows_at_workgroup_edges(P, tmpl, shape, n):
             assert np.array_equal(got[offset: offset + n * width].reshape(n, width), want)
             assert (got[:offset] == -7).all() and (got[offset + n * width:] == -7).all()
             assert P.at_space_errors(sp) == int(bad.sum())
+
+
+@pytest.mark.parametrize("tmpl,shape,form,width", [(1, CONV, "full", 208), (1, CONV, "relation", 192), (0, GEMM, "onehot", 240)])
+def test_rows_past_the_caches(P, tmpl, shape, form, width):
+    """Outputs above 320 MB, whose blocks an XCD takes 16 at a time, the last
+    blocks of the grid in order: every row is written, and by its own block
+    (the rows of the same indices in calls below that size)."""
+    import torch
+    n = (320 << 20) // (4 * width) // 64 * 64 + 64 * 37 + 5
+    print(f"[gpu-extract] template {tmpl} {form} n {n}", flush=True)
+    sp = P.at_space_create(tmpl, shape)
+    f = {"full": P.at_extract_features_full, "onehot": P.at_extract_features_onehot,
+         "relation": P.at_extract_relation_features}[form]
+    cfgs = torch.randint(0, sp.n_configs, (n,), dtype=torch.int64, device=DEV)
+    out = torch.full((n, width), -7, dtype=torch.int32, device=DEV)
+    f(sp, cfgs, out)
+    part = 100003
+    for lo in range(0, n, part):
+        c = cfgs[lo: lo + part].clone()
+        want = torch.full((len(c), width), -9, dtype=torch.int32, device=DEV)
+        f(sp, c, want)
+        assert torch.equal(out[lo: lo + part], want)
