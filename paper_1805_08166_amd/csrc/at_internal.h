@@ -194,8 +194,8 @@ struct at_space_s {
     std::vector<at::SpaceDesc> descs;       // host copies
     std::vector<int64_t> chain_offsets;     // [n_spaces + 1] (sets only)
     at::DeviceBuf d_descs;                  // SpaceDesc[n_spaces]
-    at::DeviceBuf d_factors;                // uint64 split factor tables (single spaces)
-    at::DeviceBuf d_suffix;                 // the same choices as suffix products (field l: levels l and inside)
+    at::DeviceBuf d_factors;                // uint64 split choices (single spaces), then the same choices as ...
+    const uint64_t* suffix = nullptr;       // ... suffix products (field l: levels l and inside), in d_factors
     at::DeviceBuf d_offsets;                // int64 [n_spaces + 1]
     at::DeviceBuf d_errors;                 // uint64 out-of-range counter
     // LDS images of the member spaces (stage_stride bytes apart, 0 when no

@@ -760,7 +760,7 @@ hipError_t launch_sa_local(const at_space_s& sp, const EnsembleDesc& e, at_chain
     a.descs = static_cast<const SpaceDesc*>(sp.d_descs.p);
     a.offsets = static_cast<const int64_t*>(sp.d_offsets.p);
     a.n_spaces = sp.n_spaces;
-    a.suffix = static_cast<const uint64_t*>(sp.d_suffix.p);
+    a.suffix = sp.suffix;
     a.knobs = static_cast<uint16_t*>(ch.d_knobs.p);
     a.cur_score = static_cast<float*>(ch.d_score.p);
     a.top = static_cast<at_entry*>(ch.d_top.p);

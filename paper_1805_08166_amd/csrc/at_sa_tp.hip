@@ -1612,7 +1612,7 @@ hipError_t launch_sa_tp(const at_space_s& sp, const EnsembleDesc& e, const Ensem
     ca.descs = static_cast<const SpaceDesc*>(sp.d_descs.p);
     ca.offsets = static_cast<const int64_t*>(sp.d_offsets.p);
     ca.n_spaces = sp.n_spaces;
-    ca.suffix = static_cast<const uint64_t*>(sp.d_suffix.p);
+    ca.suffix = sp.suffix;
     ca.stage = static_cast<const uint8_t*>(sp.d_stage.p);
     ca.stage_stride = sp.stage_stride;
     ca.stage_single = sp.stage_single;
