@@ -248,10 +248,8 @@ __device__ __forceinline__ void loop_features(const SpaceDesc& sd, const uint64_
     for (int a = 0; a < A; ++a) {
         at[a] = 4u * ((uint32_t)sd.split_off[a] + kv[a]) + ((level_table<TMPL>(a) >> (2 * p)) & 3u);
         r[a] = f16[at[a]];
-        if constexpr (true) {
-            constexpr auto none = [](int ax) { return outside_table<TMPL>(ax); };
-            if (none(a) != 0u) r[a] = ((none(a) >> p) & 1u) ? 1u : r[a];
-        }
+        const uint32_t inner = outside_table<TMPL>(a);   // the loops inside every level of axis a: range 1
+        if (inner != 0u) r[a] = ((inner >> p) & 1u) ? 1u : r[a];
     }
     // loop p's own axis: its range at and strictly inside p (1 inside the
     // innermost of four levels; both axes for a fused loop)
