@@ -21,13 +21,19 @@ def P():
     return paper_1805_08166_amd
 
 
-@pytest.mark.parametrize("n,trees,depth", [
-    (5, 1, 1), (40, 7, 3), (40, 300, 8), (256, 447, 6), (256, 449, 6), (130, 1000, 6),        # one chain
-    (300, 223, 6), (300, 225, 4), (300, 600, 7), (511, 520, 5),                               # two
-    (1021, 96, 8), (1000, 112, 8), (1000, 113, 6), (1000, 255, 5), (1000, 257, 8), (1000, 520, 8), (520, 1000, 4),
-    (40, 700, 9), (1000, 200, 10), (2000, 600, 8)])                                           # streamed tops
+# n, trees, depth, then what the plan is to be: chains and threads a workgroup,
+# and whole trees resident, tree tops resident ("tail") or streamed ("stream")
+@pytest.mark.parametrize("n,trees,depth,cpb,threads,form", [
+    (5, 1, 1, 1, 512, "whole"), (40, 7, 3, 1, 512, "whole"), (40, 300, 8, 1, 512, "tail"),
+    (256, 447, 6, 1, 512, "tail"), (256, 449, 6, 1, 512, "tail"), (130, 1000, 6, 1, 512, "tail"),
+    (300, 223, 6, 2, 512, "whole"), (300, 225, 4, 2, 512, "whole"), (300, 600, 7, 2, 1024, "tail"),
+    (511, 520, 5, 2, 1024, "whole"),
+    (1021, 96, 8, 4, 512, "whole"), (1000, 112, 8, 4, 512, "tail"), (1000, 113, 6, 4, 512, "whole"),
+    (1000, 255, 5, 4, 512, "whole"), (1000, 257, 8, 4, 1024, "tail"), (1000, 520, 8, 4, 1024, "tail"),
+    (520, 1000, 4, 4, 1024, "whole"),
+    (40, 700, 9, 1, 512, "stream"), (1000, 200, 10, 4, 512, "stream"), (2000, 600, 8, 8, 512, "stream")])
 @pytest.mark.parametrize("tmpl,shape", [(0, (24, 36, 30)), (3, (1, 4, 8, 8, 6, 3, 3, 1, 1))])
-def test_runs_at_plan_edges(P, tmpl, shape, n, trees, depth):
+def test_runs_at_plan_edges(P, tmpl, shape, n, trees, depth, cpb, threads, form):
     import torch
     print(f"[gpu-single] template {tmpl} chains {n} trees {trees} depth {depth}", flush=True)
     sp, osp = P.at_space_create(tmpl, shape), oracle.Space(tmpl, shape)
@@ -54,4 +60,7 @@ def test_runs_at_plan_edges(P, tmpl, shape, n, trees, depth):
         assert np.array_equal(top["cfg"], och.top["cfg"]) and np.array_equal(top["flag"], och.top["valid"])
         assert np.array_equal(top["score"].view(np.uint32), och.top["score"].view(np.uint32))
         base += steps
-    assert P.at_chains_last_path(ch) == P.AT_SA_PATH_LOCAL
+    plan = P.at_chains_last_plan(ch)
+    assert plan["path"] == P.AT_SA_PATH_LOCAL
+    assert (plan["chains_per_wg"], plan["threads"]) == (cpb, threads)
+    assert (plan["chunks"] > 1, plan["gather"]) == {"whole": (False, 0), "tail": (False, 2), "stream": (True, 1)}[form]
