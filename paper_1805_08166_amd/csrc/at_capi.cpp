@@ -15,10 +15,19 @@ namespace {
 thread_local std::string g_last_error;
 
 // Whether a run takes the chain-local path by default: up to 768 KB a step
-// and workgroup from outside its LDS.  A plan that streams tree tops counts
-// its whole node blocks: at 642 KB of tops (500 trees of depth 10, 1024
-// chains) it takes 16.5 us a step and the tree-partitioned path 13.3, at 578
-// KB 15.3 and 13.6.
+// and workgroup from outside its LDS; a plan that streams tree tops counts
+// its whole node blocks.  Measured on the 512^3 GEMM space, us a step,
+// chain-local then tree-partitioned: 1024 chains x 1000 trees of depth 8 11.7
+// and 16.0, 2048 x 1000 of depth 4 13.0 and 17.1, both chain-local; 1024 x 500
+// of depth 10 (642 KB of tops and tail records, 1154 KB counted) 13.9 and
+// 13.2, tree-partitioned.  Bytes leave out the walk and the chunks, so some
+// searches take the slower path:
+//  - Sixteen or more chains a workgroup and many chunks run chain-local: 4096
+//    x 1000 of depth 4 22.3 and 20.7, x 2000 41.3 and 28.7; 8192 x 1000 of
+//    depth 6 50.3 and 24.5; 16384 x 500 of depth 8 59.6 and 30.5.
+//  - Few chains a workgroup and large ensembles run tree-partitioned: 256 x
+//    2000 of depth 8 14.3 and 19.9, 1024 x 2000 18.6 and 23.6, 1024 x 1000 of
+//    depth 9 14.6 and 16.2.
 bool local_by_default(const LocalPlan& pl, const EnsembleDesc& e) {
     double bytes = pl.round_bytes;
     if (pl.gather && e.depth >= 2) bytes += 4.0 * e.n_trees * (1 << (e.depth - 2));
@@ -920,7 +929,7 @@ static at_status sa_run_impl(at_space_t space, at_ensemble_t ens, at_ensemble_t 
         return fail(AT_E_UNSUPPORTED, f + ": step counter must fit 32 bits");
     DeviceGuard g(chains->device);
     const bool init = !chains->initialised;
-    // path: chain-local when its plan fits and is the faster one, else
+    // path: chain-local when its plan fits and local_by_default takes it, else
     // tree-partitioned; Eq. 4 runs take the tree-partitioned path
     LocalPlan pl;
     const bool local_fits = !global && chains->n_chains > 0 && plan_local(*space, ens->desc, *chains, pl);
