@@ -29,9 +29,11 @@ using namespace dev;
 // One configuration a lane and 256 a workgroup left both a longer serial
 // chain and, with up to 99 KB of LDS a workgroup, too few workgroups to keep
 // the stores going: 200003 conv2d rows took 33.8 us in the 208-column form
-// and 75.7 in the 384-column one against 29.2 and 51.7 (5.7 and 5.9 TB/s);
-// 2^20 rows of 176 take 146 us either way, the rate of sustained writes.
-// Non-temporal stores measured 62 us on the 384-column rows.
+// and 75.7 in the 384-column one against 29.2 and 51.7 (5.7 and 5.9 TB/s),
+// one buffer written again and again, part of it still in the cache behind
+// the L2s; the two forms in turn, 473 MB, take 34.4 and 58.8.  2^20 rows of
+// 176 take 143 us, the rate of sustained writes.  Non-temporal stores
+// measured 62 us on the 384-column rows.
 // ==========================================================================
 constexpr int ROWS = 64;               // configurations per workgroup
 constexpr int WAVES = WG / 64;

@@ -37,8 +37,8 @@ using namespace dev;
 
 constexpr int LOCAL_WG_MAX = 512;
 constexpr int LOCAL_FAC_MAX = 1024;          // split choices staged in LDS
-// dynamic LDS per workgroup: the compute unit's 160 KB less 1 KB kept for
-// any static LDS the compiler places
+// dynamic LDS per workgroup: the compute unit's 160 KB less 1 KB; the launch
+// checks that the kernel has no static LDS
 constexpr size_t LOCAL_LDS_BYTES = 163840 - 1024;
 
 struct LocalArgs {

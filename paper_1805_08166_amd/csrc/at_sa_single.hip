@@ -35,8 +35,8 @@ namespace {
 using namespace dev;
 
 constexpr int SINGLE_FAC_MAX = 1024;          // split choices staged in LDS
-// dynamic LDS per workgroup: the compute unit's 160 KB less 1 KB kept for
-// any static LDS the compiler places
+// dynamic LDS per workgroup: the compute unit's 160 KB less 1 KB; the launch
+// checks that the kernel has no static LDS
 constexpr size_t SINGLE_LDS_BYTES = 163840 - 1024;
 
 // One chain's record.  Rounds are numbered from 0 (the initial draw, when

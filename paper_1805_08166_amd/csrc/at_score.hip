@@ -34,9 +34,10 @@ constexpr int SWG = 256;
 // One lane a row (k_score, the only way before) leaves the chip idle below
 // some 200 K rows: every row's trees are one lane's chain of dependent LDS
 // reads.  Here the chain is a chunk's walk, then the fold's dependent adds.
-// Measured, one call (one lane a row -> this): 64 rows x 500 trees of depth 8
-// on 176 features 111 -> 5 us; 4099 rows of the same 130 -> 13; 20011 rows x
-// 500 trees on 110 features 230 -> 33; 65537 rows x 1000 trees 236 -> 158.
+// Measured, calls one after another (one lane a row -> this): 64 rows x 500
+// trees of depth 8 on 176 features 111 -> 8 us; 4099 rows of the same 130 ->
+// 14; 20011 rows x 500 trees on 110 features 230 -> 33; 65537 rows x 1000
+// trees 236 -> 156 (169 for a launch the card is idle before).
 // Small batches are bound by the fold (500 adds at about 9 clocks each) and
 // the stream of the tree tops; large ones by the tail gathers (64 lanes take
 // 64 clocks of a compute unit's address path per tree) and the LDS reads.
@@ -363,7 +364,8 @@ hipError_t launch_score_wide(const EnsembleDesc& e, const int32_t* feats, int64_
 
 namespace {
 
-// Dynamic LDS a scoring workgroup may use: the compute unit's 160 KB less 1 KB.
+// Dynamic LDS a scoring workgroup may use: the compute unit's 160 KB less 1 KB
+// (no static LDS, as the launch checks).
 constexpr size_t SCORE_LDS_BYTES = 163840 - 1024;
 
 struct RowsPlan {
@@ -391,13 +393,17 @@ bool rows_layout(const EnsembleDesc& e, RowsPlan& pl, RowsArgs& a, size_t limit)
 
 // Plan of k_rows.  The lines lie where a sweep of rows a workgroup, waves,
 // chunk and form (n 16 .. 300000, depths 4 .. 10, 100 .. 1500 trees, 110 and
-// 176 features) put them; its plans are within 5 % of the sweep's best in
-// the geometric mean.
+// 176 features) put them; over it the plans are within 5 % of the best in the
+// geometric mean, and further off just past a line (below).
 //  - Rows a workgroup: 8 up to 2048 rows (a workgroup streams the whole
-//    ensemble, so fewer rows a workgroup only repeat that), then as many as
-//    leave a workgroup for each of 256 compute units, up to 32; 64 when even
-//    so the chip is full several times over (above 24576 rows; above 12288
-//    for deep trees, whose streaming costs more).
+//    ensemble, so fewer rows a workgroup only repeat that), then doubled, up
+//    to 32, until 256 workgroups at most are left; 64 when even so the chip
+//    is full several times over (above 24576 rows; above 12288 for deep
+//    trees, whose streaming costs more).  Just past a line half the compute
+//    units have no workgroup, or each has two of half the LDS (500 trees of
+//    depth 8 on 176 features, us, with leaf indices in brackets): 2048 rows
+//    9.1 (10.0), 2049 9.8 (12.3); 4096 11.1 (13.9), 4097 14.3 (19.1); 8192
+//    14.8 (23.2), 8193 21.1 (25.4); 24576 32.3 (53.6), 24577 37.7 (79.1).
 //  - Up to one workgroup a compute unit: 16 waves and all of its LDS; more:
 //    12 waves and half of it, 8 waves from 98304 rows (500 trees of depth 8
 //    on 176 features, 4099 rows: 14.3 us with 16 waves, 17.4 with 6; 131072
