@@ -35,6 +35,8 @@ namespace {
 using namespace dev;
 
 constexpr int SINGLE_FAC_MAX = 1024;          // split choices staged in LDS
+constexpr int SINGLE_CHAINS = 4;              // chains per workgroup at most
+constexpr int SINGLE_WIDE_WALKS = 1024;       // tree walks a round above which a workgroup has 1024 threads
 // dynamic LDS per workgroup: the compute unit's 160 KB less 1 KB; the launch
 // checks that the kernel has no static LDS
 constexpr size_t SINGLE_LDS_BYTES = 163840 - 1024;
@@ -566,8 +568,13 @@ hipError_t launch_single_nt(const SingleArgs& a, const LocalPlan& pl, hipStream_
 
 template <int TMPL, int DEPTH, bool TAIL>
 hipError_t launch_single_t(const SingleArgs& a, const LocalPlan& pl, hipStream_t stream) {
-    return pl.threads == 1024 ? launch_single_nt<TMPL, DEPTH, TAIL, 1024>(a, pl, stream)
-                              : launch_single_nt<TMPL, DEPTH, TAIL, 512>(a, pl, stream);
+    // 1024 threads are for more than 1024 walks of at most four chains, and
+    // 257 whole trees of depth 7, or tops of depth 10, do not fit the LDS
+    if constexpr ((SINGLE_WIDE_WALKS / SINGLE_CHAINS + 1) * local_stride(DEPTH, TAIL) * 4 <= (int)SINGLE_LDS_BYTES) {
+        if (pl.threads == 1024) return launch_single_nt<TMPL, DEPTH, TAIL, 1024>(a, pl, stream);
+    }
+    if (pl.threads != 512) return hipErrorInvalidConfiguration;
+    return launch_single_nt<TMPL, DEPTH, TAIL, 512>(a, pl, stream);
 }
 
 template <int TMPL, bool TAIL>
@@ -597,7 +604,7 @@ hipError_t launch_single_d(const SingleArgs& a, const LocalPlan& pl, int depth, 
 // a pass: 1024 threads when 512 would give it more than two (the C2 search,
 // 2000 tree walks a round: 1685 us a run against 1790).
 bool plan_single(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s& ch, LocalPlan& pl) {
-    if (pl.cpb > 4) return false;
+    if (pl.cpb > SINGLE_CHAINS) return false;
     const int64_t n = ch.n_chains;
     const int RS = (sp.descs[0].n_features + 3) / 4 * 4 + 4;
     int fac_max = 0;
@@ -634,7 +641,7 @@ bool plan_single(const at_space_s& sp, const EnsembleDesc& e, const at_chains_s&
         pl.ts = ts;
         pl.ct = T;
         pl.n_chunks = 1;
-        pl.threads = T * pl.cpb > 1024 ? 1024 : 512;
+        pl.threads = T * pl.cpb > SINGLE_WIDE_WALKS ? 1024 : 512;
         // the evaluating waves stay out of the walk when that costs no pass
         const int ew = (pl.cpb + 1) / 2;
         auto passes = [&](int lanes) {

@@ -31,6 +31,8 @@ def P():
     (1021, 96, 8, 4, 512, "whole"), (1000, 112, 8, 4, 512, "tail"), (1000, 113, 6, 4, 512, "whole"),
     (1000, 255, 5, 4, 512, "whole"), (1000, 257, 8, 4, 1024, "tail"), (1000, 520, 8, 4, 1024, "tail"),
     (520, 1000, 4, 4, 1024, "whole"),
+    (1000, 257, 6, 4, 1024, "whole"), (1000, 257, 7, 4, 1024, "tail"), (1000, 257, 9, 4, 1024, "tail"),
+    (1000, 257, 10, 4, 512, "stream"),                   # the deepest of either form at 1024 threads, and past them
     (40, 700, 9, 1, 512, "stream"), (1000, 200, 10, 4, 512, "stream"), (2000, 600, 8, 8, 512, "stream")])
 @pytest.mark.parametrize("tmpl,shape", [(0, (24, 36, 30)), (3, (1, 4, 8, 8, 6, 3, 3, 1, 1))])
 def test_runs_at_plan_edges(P, tmpl, shape, n, trees, depth, cpb, threads, form):
